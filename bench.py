@@ -103,7 +103,7 @@ def parse():
     return p.parse_args()
 
 
-def stage_source_hash(names=("kernels_fused.hip", "mhd_math.hpp", "common.hpp")) -> str:
+def stage_source_hash(names=("stage_tile.hpp", "stage_args.hpp", "mhd_math.hpp", "common.hpp")) -> str:
     """Hash of the kernels' code (the named sources) with comments and blank
     lines removed, so that a comment edit does not invalidate the stored PMC
     traffic."""
