@@ -130,9 +130,10 @@ ATHMHD_API int athmhd_version(void);
  * one block on the current device.  nblocks_max identical blocks may later be
  * advanced together (each periodic on its own).  On success *out receives a
  * handle owned by the caller (free with athmhd_destroy).  The fused stage
- * kernel marches each workgroup over a segment of x3 planes whose length is
- * chosen per launch from the block size and the device's CU count; a positive
- * integer in the environment variable ATHMHD_KZ, read here, fixes it instead. */
+ * kernel marches each workgroup over a segment of x3 planes; its thread tile
+ * and the segment length are chosen from the block size, the block count and
+ * the device's CU count; a positive
+ * integer in the environment variable ATHMHD_KZ, read here, fixes the length. */
 ATHMHD_API int athmhd_create(const athmhd_config* cfg, int nblocks_max, athmhd_t* out);
 
 /* One full time step of nblocks (<= nblocks_max) blocks, in place:
@@ -373,7 +374,8 @@ ATHMHD_API int athmhd_batch_tune(athmhd_t h, const double* cons, const double* b
 ATHMHD_API int athmhd_set_floors(athmhd_t h, double dfloor, double pfloor);
 
 /* Number of floor activations (cells and face states) since the previous
- * call, which clears the counter.  Synchronises `stream`. */
+ * call, which clears the counter.  A cell or face that several workgroups of
+ * the stage kernel evaluate (at tile and segment edges) counts for each.  Synchronises `stream`. */
 ATHMHD_API int athmhd_floor_count(athmhd_t h, long long* count, void* stream);
 
 /* enable = 1: athmhd_step records its launches once into a hipGraph (for the

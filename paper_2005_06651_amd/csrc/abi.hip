@@ -69,7 +69,9 @@ struct athmhd_s {
   Floors floors{0.0, 0.0};                // optional primitive floors (off by default)
   double* d_dtval = nullptr;              // dt of the step on the device (graph replay)
   void* h_pinned = nullptr;               // 16 bytes of pinned host memory for newdt
-  int kz = 0;                             // x3 planes per fused workgroup (0: default)
+  int kz = 0;                             // x3 planes per fused workgroup (0: planned)
+  FusedPlan plan[3] = {};                 // plans of the fused stage per reconstruction, for plan_nb blocks
+  int plan_nb = 0;
   int cus = 0;                            // compute units of the device
   // kernel timing
   bool profiling = false;
@@ -397,8 +399,15 @@ hipError_t launch_cfl(athmhd_t h, const double* cons, const double* bface, int n
   return launch_newdt(h->g, h->cfg.gamma, cons, bface, nblocks, bits, h->floors, h->d_bad, s, floor);
 }
 
-// x3 planes per workgroup of the fused stage kernel on nblocks uniform blocks
-int stage_kz(athmhd_t h, int nblocks) { return h->kz > 0 ? h->kz : fused_default_kz(h->g, nblocks, h->cus); }
+// Plan of the fused stage kernel on nblocks uniform blocks, kept per
+// reconstruction until the block count changes.
+FusedPlan stage_plan(athmhd_t h, int recon, int nblocks) {
+  if (h->plan_nb != nblocks) {
+    for (int r = 0; r < 3; ++r) h->plan[r] = fused_plan(h->g, r, nblocks, h->cus, h->kz);
+    h->plan_nb = nblocks;
+  }
+  return h->plan[recon];
+}
 
 // One stage: uniform or batched, fused or unfused.
 hipError_t launch_stage(athmhd_t h, int recon, const double* xc, const double* xb, const double* unc,
@@ -411,7 +420,7 @@ hipError_t launch_stage(athmhd_t h, int recon, const double* xc, const double* x
                               h->d_bad, h->g.ns > 0 ? h->d_fm : nullptr, s, h->coupled);
   if (!h->unfused)
     return launch_stage_fused(h->g, h->cfg.gamma, recon, h->cfg.riemann, h->cfg.ct_eps, xc, xb, unc, unb, oc, ob, cf,
-                              dt_dev, beta, nblocks, stage_kz(h, nblocks), h->floors, h->d_bad,
+                              dt_dev, beta, nblocks, stage_plan(h, recon, nblocks), h->floors, h->d_bad,
                               h->g.ns > 0 ? h->d_fm : nullptr, s);
   return launch_stage_unfused(h->g, h->cfg.gamma, recon, h->cfg.riemann, h->cfg.ct_eps, xc, xb, unc, unb, oc, ob,
                               cf, dt_dev, beta, nblocks, h->scr, h->floors, h->d_bad, h->cfg.charac != 0, s);
@@ -1174,7 +1183,7 @@ int athmhd_step_vjp(athmhd_t h, const double* cons_n, const double* bface_n, dou
     const int recon = (h->cfg.integrator == ATHMHD_VL2 && st == 0) ? ATHMHD_RECON_DC : h->cfg.recon;
     const StageCoef cf{sc.g0[st], sc.g1[st], sc.beta[st] * dt};
     e = launch_stage_fused(g, h->cfg.gamma, recon, h->cfg.riemann, h->cfg.ct_eps, xc[st], xb[st], cons_n, bface_n,
-                           oc, ob, cf, nullptr, sc.beta[st], nblocks, stage_kz(h, nblocks), h->floors, h->d_bad,
+                           oc, ob, cf, nullptr, sc.beta[st], nblocks, stage_plan(h, recon, nblocks), h->floors, h->d_bad,
                            nullptr, s);
     if (e != hipSuccess) return hip_fail(h, e, "vjp forward stage launch");
     xc[st + 1] = oc;

@@ -97,18 +97,24 @@ hipError_t launch_level_fine_faces(const Geo& gf, const double* xb, const double
                                    const double* dt_dev, double beta, const UnfusedScratch& fine, hipStream_t s);
 
 // One stage in a single fused kernel (same contract as launch_stage_unfused);
-// kz = x3 planes per workgroup segment (0: default for the block size).
+// plan: thread tile and x3 planes per workgroup segment, from fused_plan.
 // dt_dev, if not NULL, supplies dt on the device (bdt = beta * dt).
 // bad[0] counts threads that met a non-physical cell; floor activations go to
 // the 64-bit counter of add_floor_count.
+struct FusedPlan {
+  bool small;  // 18 x 14 threads per workgroup instead of 34 x 15
+  int kz;      // x3 planes per workgroup
+};
+// the plan of a launch over nb blocks on a device of cus compute units;
+// kz_fixed > 0 prescribes the segment length
+FusedPlan fused_plan(const Geo& g, int recon, int nb, int cus, int kz_fixed);
 hipError_t launch_stage_fused(const Geo& g, double gamma, int recon, int rs, double ct_eps, const double* xc,
                               const double* xb, const double* unc, const double* unb, double* outc, double* outb,
-                              StageCoef coef, const double* dt_dev, double beta, int nb, int kz, Floors fl, int* bad,
-                              double* fm, hipStream_t s);  // kz > 0: x3 planes per workgroup
+                              StageCoef coef, const double* dt_dev, double beta, int nb, FusedPlan plan, Floors fl, int* bad,
+                              double* fm, hipStream_t s);
 // fm: NULL, or the output of the mass flux through the lower face of every
 // active cell along each direction (3 face arrays per block), for the passive
 // scalars.
-int fused_default_kz(const Geo& g, int nb, int cus);
 
 // Passive scalars of one stage (rows 5 .. 5+ns-1 of the cell arrays), after
 // the fused stage that stored the face mass fluxes fm:

@@ -1,21 +1,58 @@
 // kernels_fused.hip -- host side of the fused stage kernels: thread tile and
 // x3 segment length of a launch, and the launchers of uniform and batched
 // stages.  The kernels (stage_tile.hpp) are compiled in the stage_*.hip units.
+#include <algorithm>
+#include <cmath>
+
 #include "stage_args.hpp"
 
 namespace athmhd {
 
-int fused_default_kz(const Geo& g, int nb, int cus) {
-  // the longest x3 segment (32 planes down to 4) that still gives the launch
-  // at least 2.5 workgroups per CU: longer segments repeat less of the
-  // window start-up, more segments fill the chip on small blocks.  64 planes
-  // where that still leaves 16 workgroups per CU (512^3: 0.9 % faster with
-  // PPM; 256^3, with 2.5 per CU, 12 % slower)
-  const int64_t tiles = (int64_t)((g.n1 + TileU::TX - 1) / TileU::TX) * ((g.n2 + TileU::TY - 1) / TileU::TY) * nb;
-  if (tiles * ((g.n3 + 63) / 64) >= 16 * (int64_t)cus) return 64 < g.n3 ? 64 : g.n3;
-  int kz = 32;
-  while (kz > 4 && 2 * tiles * ((g.n3 + kz - 1) / kz) < 5 * (int64_t)cus) kz /= 2;
-  return kz < g.n3 ? kz : g.n3;
+// Workgroup rounds of a launch, in units of one round of the 34 x 15 tile (one
+// workgroup of 8 waves per CU).  Two 18 x 14 workgroups of 4 waves share a CU:
+//   * with DC and PLM a full round of them costs as much as one of the larger
+//     tile (15.9 and 16.0 us per plane of a VL2 step), with PPM 0.95 of it, and
+//     0.85 when rounds follow each other, as their barriers then fall apart
+//     (RK3 at 256^3: 59.7 and 50.6 us per plane);
+//   * one workgroup alone on each CU takes 0.75 of a round (12 us);
+//   * the last, partial round overlaps the one before it: at least half a
+//     round, else its share of the CUs (2.75 rounds at 128^3 measured 2.79,
+//     1.375 rounds 1.5).
+static double rounds_small(int64_t wgs, int cus, int recon) {
+  const double r = (double)wgs / (2.0 * cus);
+  const double full = std::floor(r), f = r - full;
+  const double tail = f == 0.0 ? 0.0 : full == 0.0 ? (f <= 0.5 ? 0.75 : 1.0) : std::max(0.5, f);
+  return (full + tail) * (recon < 2 ? 1.0 : r < 4.0 ? 0.95 : 0.85);
+}
+
+// Thread tile and x3 segment length of a launch: the pair with the least
+// planes x rounds.  A segment of kz planes costs kz + 2 plane iterations and a
+// window start-up; short segments repeat more of them, long ones leave the
+// last round of workgroups nearly empty or the chip unfilled.  Measured with
+// the rule before (34 x 15 only, kz in 4, 8, .. 32 or 64) and now, per step:
+// 64^3 VL2+PLM 98 -> 83 us, 96^3 252 -> 193 us, 192^3 1415 -> 1242 us, 32^3 RK3+PPM
+// 363 -> 150 us, 200x150x131 RK3+PPM+HLLE 3.4 -> 2.6 ms; 256^3 VL2+PLM stays on
+// 34 x 15 and 32 planes (2.75 ms; 18 x 14: 2.94), RK3+PPM 10.1 -> 9.5 ms.
+FusedPlan fused_plan(const Geo& g, int recon, int nb, int cus, int kz_fixed) {
+  FusedPlan best{false, 1};
+  double cost = 1e300;
+  const int64_t cols_u = (int64_t)((g.n1 + TileU::TX - 1) / TileU::TX) * ((g.n2 + TileU::TY - 1) / TileU::TY) * nb;
+  const int64_t cols_s = (int64_t)((g.n1 + TileS::TX - 1) / TileS::TX) * ((g.n2 + TileS::TY - 1) / TileS::TY) * nb;
+  const int lo = kz_fixed > 0 ? kz_fixed : 1, hi = kz_fixed > 0 ? kz_fixed : std::min(g.n3, 128);
+  for (int kz = lo; kz <= hi; ++kz) {
+    const int nseg = (g.n3 + kz - 1) / kz;
+    const double planes = std::min(kz, g.n3) + 2.5;
+    const double u = planes * (double)((cols_u * nseg + cus - 1) / cus), v = planes * rounds_small(cols_s * nseg, cus, recon);
+    if (u < cost) {
+      cost = u;
+      best = FusedPlan{false, kz};
+    }
+    if (v < cost) {
+      cost = v;
+      best = FusedPlan{true, kz};
+    }
+  }
+  return best;
 }
 
 static StageArgs make_stage_args(double gamma, double ct_eps, StageCoef coef, const double* dt_dev, double beta,
@@ -31,24 +68,30 @@ static StageArgs make_stage_args(double gamma, double ct_eps, StageCoef coef, co
   return sa;
 }
 
+template <class T>
+static hipError_t launch_uniform_recon(int recon, int rs, const UniformArgs& fa, hipStream_t s) {
+  if (recon == 0) return launch_uniform<0, T>(rs, fa, s);
+  if (recon == 1) return launch_uniform<1, T>(rs, fa, s);
+  return launch_uniform<2, T>(rs, fa, s);
+}
+
 hipError_t launch_stage_fused(const Geo& g, double gamma, int recon, int rs, double ct_eps, const double* xc,
                               const double* xb, const double* unc, const double* unb, double* outc, double* outb,
-                              StageCoef coef, const double* dt_dev, double beta, int nb, int kz, Floors fl, int* bad,
+                              StageCoef coef, const double* dt_dev, double beta, int nb, FusedPlan plan, Floors fl, int* bad,
                               double* fm, hipStream_t s) {
   UniformArgs fa;
   fa.g = g;
   fa.sa = make_stage_args(gamma, ct_eps, coef, dt_dev, beta, fl, bad);
   fa.xc = xc; fa.xb = xb; fa.unc = unc; fa.unb = unb; fa.oc = outc; fa.ob = outb;
   fa.fm = fm;
-  fa.kz = kz;
-  fa.ntx = (g.n1 + TileU::TX - 1) / TileU::TX;
-  fa.nty = (g.n2 + TileU::TY - 1) / TileU::TY;
+  fa.kz = plan.kz;
+  const int TX = plan.small ? TileS::TX : TileU::TX, TY = plan.small ? TileS::TY : TileU::TY;
+  fa.ntx = (g.n1 + TX - 1) / TX;
+  fa.nty = (g.n2 + TY - 1) / TY;
   fa.nseg = (g.n3 + fa.kz - 1) / fa.kz;
   fa.total = (int64_t)fa.ntx * fa.nty * fa.nseg * nb;
   fa.per_xcd = (fa.total + 7) / 8;
-  if (recon == 0) return launch_uniform<0, TileU>(rs, fa, s);
-  if (recon == 1) return launch_uniform<1, TileU>(rs, fa, s);
-  return launch_uniform<2, TileU>(rs, fa, s);
+  return plan.small ? launch_uniform_recon<TileS>(recon, rs, fa, s) : launch_uniform_recon<TileU>(recon, rs, fa, s);
 }
 
 int batch_tile_count() { return 4; }

@@ -15,10 +15,13 @@ template <int BX_, int BY_>
 struct Tile {
   static constexpr int BX = BX_, BY = BY_, NT = BX_ * BY_, TX = BX_ - 2, TY = BY_ - 2;
 };
-// uniform blocks: 32 x 13 active columns in one 8-wave workgroup per CU; of
-// the tiles that fit the register and LDS budget this one keeps the largest
-// share of lanes on active columns on large blocks (80 % at 256^3)
+// Uniform blocks run on one of two tiles (fused_plan picks): 32 x 13 active
+// columns in one 8-wave workgroup per CU, which keeps the largest share of
+// lanes on active columns (82 %; 80 % at 256^3), or 16 x 12 in a 4-wave
+// workgroup, two to a CU (76 %): half the granule, and neither workgroup waits
+// at the other's barriers.
 using TileU = Tile<34, 15>;
+using TileS = Tile<18, 14>;
 
 // Arguments shared by every tile of a stage.
 struct StageArgs {

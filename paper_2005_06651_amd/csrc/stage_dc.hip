@@ -3,4 +3,5 @@
 
 namespace athmhd {
 template hipError_t launch_uniform<0, TileU>(int, const UniformArgs&, hipStream_t);
+template hipError_t launch_uniform<0, TileS>(int, const UniformArgs&, hipStream_t);
 }  // namespace athmhd

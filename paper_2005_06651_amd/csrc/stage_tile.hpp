@@ -1,12 +1,12 @@
 // stage_tile.hpp -- one stage of the MHD update in a single kernel.
 //
-// Each workgroup (34 x 15 threads, 8 wave64s) owns a tile of 32 x 13 active
-// columns in (x1, x2) plus a one-cell ring, and marches along x3 over a
-// segment of KZ planes.  Per plane everything stays on chip:
-//   * every thread owns one column of the 34 x 15 region; it converts its
-//     column's conserved state to primitives (Sec. 3.1) one plane ahead of use
-//     and keeps a short window of planes in registers for the reconstruction
-//     along x3;
+// Each workgroup (34 x 15 threads, 8 wave64s, or one of the smaller tiles of
+// stage_args.hpp) owns a tile of 32 x 13 active columns in (x1, x2) plus a
+// one-cell ring, and marches along x3 over a segment of KZ planes.  Per plane
+// everything stays on chip:
+//   * every thread owns one column of the region; it converts its column's
+//     conserved state to primitives (Sec. 3.1) one plane ahead of use and keeps
+//     a short window of planes in registers for the reconstruction along x3;
 //   * the primitives of the current plane, plus LA extra rings, go to LDS for
 //     the reconstructions along x1 and x2 (DC / PLM / PPM, Sec. 3.2.1);
 //   * each thread solves the Riemann problems (HLLD / HLLE, Sec. 3.2.2) on the

@@ -1,0 +1,51 @@
+"""The fused stage on block shapes at the edges of both thread tiles (16 x 12
+and 32 x 13 active columns), one column more and one less, with few and many
+x3 planes, so that either tile, one-plane segments, a ragged last segment and
+workgroups mostly outside the block are met; against the CPU oracle.
+
+Bar: relative L1 1e-12 per array, element by element 1e-10 (the bars of the
+other parity tests: a few hundred operations in double precision per cell and
+stage, contracted on one side only)."""
+import numpy as np
+import pytest
+
+from paper_2005_06651_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("integ,recon", [("vl2", "plm"), ("rk3", "ppm"), ("rk1", "dc")])
+@pytest.mark.parametrize("n", [(16, 12, 1), (15, 11, 3), (17, 13, 4), (32, 13, 9), (33, 14, 2), (64, 66, 64),
+                               (5, 140, 6)])
+def test_tile_edges_match_oracle(athmhd_gpu, orc, n, integ, recon):
+    torch, athmhd = athmhd_gpu
+    b = inputs.smooth_random(n=n, seed=sum(n), ng=3)
+    kw = dict(integrator=integ, recon=recon, riemann="hlld")
+    s, cfg = athmhd.Solver(b.n, b.ng, b.dx, b.gamma, **kw), orc.cfg_for(b, **kw)
+    cons = orc.prim2cons(cfg, b.prim, b.bface)
+    dev = torch.device("cuda:0")
+    tc, tb = torch.from_numpy(cons).to(dev), torch.from_numpy(b.bface).to(dev)
+    rc, rb = cons.copy(), b.bface.copy()
+    for _ in range(2):
+        dt, _ = orc.newdt(cfg, rc, rb)
+        assert orc.step(cfg, rc, rb, dt) == 0
+        s.step(tc, tb, dt)
+    a = b.active
+    scale = np.mean([np.abs(rb[c][a]).mean() for c in range(3)])
+    for got, ref, floor in ((tc.cpu().numpy(), rc, 0.0), (tb.cpu().numpy(), rb, scale)):
+        for x, y in zip(got, ref):
+            x, y = x[a], y[a]
+            mean = max(np.abs(y).mean(), floor)
+            assert np.abs(x - y).mean() <= 1e-12 * mean
+            assert np.max(np.abs(x - y) / (np.abs(y) + mean)) <= 1e-10
+    s.close()
+
+
+@pytest.fixture(scope="module")
+def athmhd_gpu():
+    import torch
+
+    from paper_2005_06651_amd import athmhd
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    athmhd.lib()
+    return torch, athmhd
