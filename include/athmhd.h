@@ -118,8 +118,10 @@ typedef struct {
  * the left eigenvectors of that cell's state (normal field: the cell-centred
  * one), reconstructed per wave family (van Leer slope, or the limited PPM
  * parabola) and projected back with the right eigenvectors (normalised after
- * Roe & Balsara 1996).  DC (the VL2 predictor) is unchanged.  Such a handle
- * runs the stages on the unfused kernel pipeline whatever kernel_path says.
+ * Roe & Balsara 1996).  DC (the VL2 predictor) is unchanged.  With PPM,
+ * or DC configured, such a handle runs its stages (but for the DC predictor)
+ * on the unfused kernel pipeline whatever kernel_path says.  A step leaves the
+ * ghost entries of its input filled.
  * ATHMHD_EUNSUP with passive scalars, on athmhd_create_mesh and
  * athmhd_create_batch, and from athmhd_step_vjp. */
 

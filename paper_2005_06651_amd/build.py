@@ -12,9 +12,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libathmhd.so")
-SOURCES = ["batch_ppm.hip", "stage_ppm.hip", "batch_plm.hip", "stage_plm.hip", "batch_dc.hip", "stage_dc.hip", "abi.hip",
-           "kernels_basic.hip", "kernels_unfused.hip", "kernels_fused.hip", "kernels_adjoint.hip", "kernels_scalar.hip",
-           "kernels_amr.hip", "kernels_levels.hip"]
+SOURCES = ["batch_ppm.hip", "stage_ppm.hip", "batch_plm.hip", "stage_plm.hip", "batch_dc.hip", "stage_charac.hip", "stage_dc.hip",
+           "abi.hip", "kernels_basic.hip", "kernels_unfused.hip", "kernels_fused.hip", "kernels_adjoint.hip",
+           "kernels_scalar.hip", "kernels_amr.hip", "kernels_levels.hip"]
 OBJDIR = os.path.join(ROOT, "_build")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

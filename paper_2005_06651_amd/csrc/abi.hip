@@ -29,8 +29,8 @@ struct athmhd_s {
   // coupled mesh (athmhd_create_mesh): the nbmax blocks tile one periodic
   // domain as g.mesh[0] x g.mesh[1] x g.mesh[2]
   bool mesh = false;
-  // the unfused pipeline runs the stages (kernel_path 1, or characteristic
-  // reconstruction, which only that pipeline implements)
+  // the unfused pipeline runs stages of this handle (kernel_path 1, a two-level
+  // composite, or characteristic reconstruction other than PLM)
   bool unfused = false;
   // two-level composite (athmhd_create_levels): block 0 coarse (geometry g,
   // with mesh[0] = -1), blocks 1..8 fine (geometry gf, widths dx / 2)
@@ -409,6 +409,17 @@ FusedPlan stage_plan(athmhd_t h, int recon, int nblocks) {
   return h->plan[recon];
 }
 
+// Whether a stage of the given reconstruction runs on the unfused pipeline.
+// Characteristic PLM and the donor-cell predictor beside characteristic PLM or
+// PPM run fused; characteristic PPM does not (its eigenvector split beside the
+// five-plane window spills 157 registers of the fused kernel, and one variant
+// of it, HLLE without floors, came out of the compiler wrong), nor does a
+// handle configured with donor cell, which keeps the pipeline's results.
+bool stage_unfused(athmhd_t h, int recon) {
+  if (h->cfg.kernel_path == 1 || h->levels) return true;
+  return h->unfused && !(h->cfg.recon == ATHMHD_RECON_PPM && recon == ATHMHD_RECON_DC);
+}
+
 // One stage: uniform or batched, fused or unfused.
 hipError_t launch_stage(athmhd_t h, int recon, const double* xc, const double* xb, const double* unc,
                         const double* unb, double* oc, double* ob, StageCoef cf, double beta, const double* dt_dev,
@@ -418,10 +429,10 @@ hipError_t launch_stage(athmhd_t h, int recon, const double* xc, const double* x
     return launch_stage_batch(h->shape, h->cfg.gamma, recon, h->cfg.riemann, h->cfg.ct_eps, h->d_desc, h->d_items,
                               h->nitems, h->d_queue, xc, xb, unc, unb, oc, ob, cf, dt_dev, beta, h->grid, h->floors,
                               h->d_bad, h->g.ns > 0 ? h->d_fm : nullptr, s, h->coupled);
-  if (!h->unfused)
+  if (!stage_unfused(h, recon))
     return launch_stage_fused(h->g, h->cfg.gamma, recon, h->cfg.riemann, h->cfg.ct_eps, xc, xb, unc, unb, oc, ob, cf,
                               dt_dev, beta, nblocks, stage_plan(h, recon, nblocks), h->floors, h->d_bad,
-                              h->g.ns > 0 ? h->d_fm : nullptr, s);
+                              h->g.ns > 0 ? h->d_fm : nullptr, h->cfg.charac != 0, s);
   return launch_stage_unfused(h->g, h->cfg.gamma, recon, h->cfg.riemann, h->cfg.ct_eps, xc, xb, unc, unb, oc, ob,
                               cf, dt_dev, beta, nblocks, h->scr, h->floors, h->d_bad, h->cfg.charac != 0, s);
 }
@@ -454,7 +465,7 @@ int enqueue_step(athmhd_t h, double* cons, double* bface, double dt, const doubl
   // the fused kernels read periodic images directly; the unfused pipeline
   // and the blocks of a coupled mesh or batch read ghost entries, which are
   // filled (exchanged between the blocks) before each stage
-  const bool ghosts = (h->unfused && !h->batch) || h->mesh || h->coupled;
+  const bool exchange = h->mesh || h->coupled;
   const int64_t ncell = h->batch ? h->ctot : h->g.cblock * nblocks;
   const int64_t nface = h->batch ? h->ftot : h->g.fblock * nblocks;
   if (sc.nstage == 1) {
@@ -469,13 +480,16 @@ int enqueue_step(athmhd_t h, double* cons, double* bface, double dt, const doubl
   for (int st = 0; st < sc.nstage; ++st) {
     // the VL2 predictor always uses donor-cell fluxes (Sec. 3.2.3)
     const int recon = (h->cfg.integrator == ATHMHD_VL2 && st == 0) ? ATHMHD_RECON_DC : h->cfg.recon;
-    // the fused stage reads recon + 1 cells past the block (the reconstruction
-    // stencil of the ring faces); the unfused pipeline reads every ghost layer
-    const int depth = h->unfused ? 0 : recon + 1;
+    // a handle with the unfused pipeline or characteristic reconstruction
+    // fills every ghost layer, of its input also where that stage is fused; a
+    // fused stage that exchanges reads recon + 1 cells past the block (the
+    // reconstruction stencil of the ring faces)
+    const bool all_layers = !h->batch && (stage_unfused(h, recon) || (h->cfg.charac && st == 0));
+    const int depth = all_layers ? 0 : recon + 1;
     // a chained step on a coupled batch takes its input's shell entries as
     // current: every step ends with an exchange of its output
     const bool current = h->coupled && dt_bits && st == 0;
-    if (ghosts && !current &&
+    if ((exchange || all_layers) && !current &&
         (e = fill_ghosts(h, const_cast<double*>(xc), const_cast<double*>(xb), nblocks, s, depth)) != hipSuccess)
       return hip_fail(h, e, "fill_ghosts launch");
     const bool last = st == sc.nstage - 1;
@@ -661,7 +675,7 @@ int athmhd_create(const athmhd_config* cfg, int nblocks_max, athmhd_t* out) {
   h->cfg = *cfg;
   h->g = make_geo(cfg->n1, cfg->n2, cfg->n3, cfg->nghost, cfg->dx1, cfg->dx2, cfg->dx3, cfg->nscalars);
   h->nbmax = nblocks_max;
-  h->unfused = cfg->kernel_path == 1 || cfg->charac;
+  h->unfused = cfg->kernel_path == 1 || (cfg->charac && cfg->recon != ATHMHD_RECON_PLM);
   read_env(h);
   hipError_t e = hipGetDevice(&h->device);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&h->cus, hipDeviceAttributeMultiprocessorCount, h->device);
@@ -1184,7 +1198,7 @@ int athmhd_step_vjp(athmhd_t h, const double* cons_n, const double* bface_n, dou
     const StageCoef cf{sc.g0[st], sc.g1[st], sc.beta[st] * dt};
     e = launch_stage_fused(g, h->cfg.gamma, recon, h->cfg.riemann, h->cfg.ct_eps, xc[st], xb[st], cons_n, bface_n,
                            oc, ob, cf, nullptr, sc.beta[st], nblocks, stage_plan(h, recon, nblocks), h->floors, h->d_bad,
-                           nullptr, s);
+                           nullptr, false, s);
     if (e != hipSuccess) return hip_fail(h, e, "vjp forward stage launch");
     xc[st + 1] = oc;
     xb[st + 1] = ob;

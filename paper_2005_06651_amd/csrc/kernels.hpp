@@ -111,7 +111,9 @@ FusedPlan fused_plan(const Geo& g, int recon, int nb, int cus, int kz_fixed);
 hipError_t launch_stage_fused(const Geo& g, double gamma, int recon, int rs, double ct_eps, const double* xc,
                               const double* xb, const double* unc, const double* unb, double* outc, double* outb,
                               StageCoef coef, const double* dt_dev, double beta, int nb, FusedPlan plan, Floors fl, int* bad,
-                              double* fm, hipStream_t s);
+                              double* fm, bool charac, hipStream_t s);
+// charac: PLM on characteristic variables (periodic blocks, fm NULL; DC is the
+// same with and without, PPM is refused).
 // fm: NULL, or the output of the mass flux through the lower face of every
 // active cell along each direction (3 face arrays per block), for the passive
 // scalars.

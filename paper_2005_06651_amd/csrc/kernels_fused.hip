@@ -78,7 +78,8 @@ static hipError_t launch_uniform_recon(int recon, int rs, const UniformArgs& fa,
 hipError_t launch_stage_fused(const Geo& g, double gamma, int recon, int rs, double ct_eps, const double* xc,
                               const double* xb, const double* unc, const double* unb, double* outc, double* outb,
                               StageCoef coef, const double* dt_dev, double beta, int nb, FusedPlan plan, Floors fl, int* bad,
-                              double* fm, hipStream_t s) {
+                              double* fm, bool charac, hipStream_t s) {
+  if (charac && recon > 0 && (recon != 1 || fm || g.mesh[0])) return hipErrorInvalidValue;
   UniformArgs fa;
   fa.g = g;
   fa.sa = make_stage_args(gamma, ct_eps, coef, dt_dev, beta, fl, bad);
@@ -91,6 +92,7 @@ hipError_t launch_stage_fused(const Geo& g, double gamma, int recon, int rs, dou
   fa.nseg = (g.n3 + fa.kz - 1) / fa.kz;
   fa.total = (int64_t)fa.ntx * fa.nty * fa.nseg * nb;
   fa.per_xcd = (fa.total + 7) / 8;
+  if (charac && recon == 1) return plan.small ? launch_charac<TileS>(rs, fa, s) : launch_charac<TileU>(rs, fa, s);
   return plan.small ? launch_uniform_recon<TileS>(recon, rs, fa, s) : launch_uniform_recon<TileU>(recon, rs, fa, s);
 }
 

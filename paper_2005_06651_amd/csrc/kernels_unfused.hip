@@ -68,175 +68,6 @@ __device__ __forceinline__ void recon_pair(const double* __restrict__ q, int s, 
   }
 }
 
-// ---- characteristic reconstruction (Sec. 3.2.1: C = L W) -------------------
-// Face frame, primitives w = (rho, vn, vt1, vt2, P, Bt1, Bt2), normal field bn.
-// Columns of R are the right eigenvectors of W_t + A W_x = 0 for the waves
-// vn - cf, vn - ca, vn - cs, vn, vn + cs, vn + ca, vn + cf, normalised after
-// Roe & Balsara (1996) (alpha_f, alpha_s from the fast and slow speeds, beta
-// along the transverse field, 1/sqrt2 each where it vanishes, alpha_f = 1 and
-// alpha_s = 0 where cf = cs), so they stay independent where speeds coincide.
-__device__ void char_right(const double* w, double bn, double gamma, double R[7][7]) {
-  const double rho = w[0], p = w[4], t1 = w[5], t2 = w[6];
-  const double a2 = gamma * p / rho, ca2 = bn * bn / rho, bt2 = t1 * t1 + t2 * t2;
-  const double sum = a2 + ca2 + bt2 / rho;
-  const double disc = fmax(sum * sum - 4.0 * a2 * ca2, 0.0);
-  const double cf2 = 0.5 * (sum + sqrt(disc));
-  const double cs2 = cf2 > 0.0 ? a2 * ca2 / cf2 : 0.0;
-  double af = 1.0, as = 0.0;
-  if (cf2 - cs2 > 0.0) {
-    af = sqrt(fmin(1.0, fmax(0.0, (a2 - cs2) / (cf2 - cs2))));
-    as = sqrt(fmin(1.0, fmax(0.0, (cf2 - a2) / (cf2 - cs2))));
-  }
-  double e1 = 0.70710678118654752440, e2 = 0.70710678118654752440;
-  if (bt2 > 0.0) {
-    const double bt = sqrt(bt2);
-    e1 = t1 / bt;
-    e2 = t2 / bt;
-  }
-  const double sg = bn >= 0.0 ? 1.0 : -1.0;
-  const double a = sqrt(a2), cf = sqrt(cf2), cs = sqrt(cs2), sr = sqrt(rho), gp = gamma * p;
-#pragma unroll
-  for (int r = 0; r < 7; ++r)
-#pragma unroll
-    for (int c = 0; c < 7; ++c) R[r][c] = 0.0;
-#pragma unroll
-  for (int side = 0; side < 2; ++side) {
-    const double m = side == 0 ? -1.0 : 1.0;  // left- or right-going
-    const int f = side == 0 ? 0 : 6, al = side == 0 ? 1 : 5, sl = side == 0 ? 2 : 4;
-    R[0][f] = rho * af;  // fast
-    R[1][f] = m * cf * af;
-    R[2][f] = -m * as * cs * e1 * sg;
-    R[3][f] = -m * as * cs * e2 * sg;
-    R[4][f] = gp * af;
-    R[5][f] = as * sr * a * e1;
-    R[6][f] = as * sr * a * e2;
-    R[2][al] = m * e2;  // Alfven
-    R[3][al] = -m * e1;
-    R[5][al] = -e2 * sg * sr;
-    R[6][al] = e1 * sg * sr;
-    R[0][sl] = rho * as;  // slow
-    R[1][sl] = m * cs * as;
-    R[2][sl] = m * af * cf * e1 * sg;
-    R[3][sl] = m * af * cf * e2 * sg;
-    R[4][sl] = gp * as;
-    R[5][sl] = -af * sr * a * e1;
-    R[6][sl] = -af * sr * a * e2;
-  }
-  R[0][3] = 1.0;  // entropy
-}
-
-// Projection onto the characteristic variables of the state w0: solves
-// R x = B for NR right-hand sides (rows of B, replaced by the solutions) by
-// Gaussian elimination with partial pivoting.  Rows are exchanged by selects
-// so that every index is a compile-time constant and the system stays in
-// registers.
-template <int NR>
-__device__ __forceinline__ void char_project(const double* w0, double bn, double gamma, double (&B)[NR][7]) {
-  double M[7][7 + NR];
-  {
-    double R[7][7];
-    char_right(w0, bn, gamma, R);
-#pragma unroll
-    for (int r = 0; r < 7; ++r) {
-#pragma unroll
-      for (int c = 0; c < 7; ++c) M[r][c] = R[r][c];
-#pragma unroll
-      for (int n = 0; n < NR; ++n) M[r][7 + n] = B[n][r];
-    }
-  }
-#pragma unroll
-  for (int c = 0; c < 7; ++c) {
-    // the largest entry of column c (rows c..6) to row c
-#pragma unroll
-    for (int r = c + 1; r < 7; ++r) {
-      const bool sw = fabs(M[r][c]) > fabs(M[c][c]);
-#pragma unroll
-      for (int k = c; k < 7 + NR; ++k) {
-        const double a = M[c][k], b = M[r][k];
-        M[c][k] = sw ? b : a;
-        M[r][k] = sw ? a : b;
-      }
-    }
-    const double inv = 1.0 / M[c][c];
-#pragma unroll
-    for (int r = c + 1; r < 7; ++r) {
-      const double f = M[r][c] * inv;
-#pragma unroll
-      for (int k = c + 1; k < 7 + NR; ++k) M[r][k] -= f * M[c][k];
-    }
-  }
-#pragma unroll
-  for (int c = 6; c >= 0; --c) {
-    const double inv = 1.0 / M[c][c];
-#pragma unroll
-    for (int n = 0; n < NR; ++n) {
-      double v = M[c][7 + n];
-#pragma unroll
-      for (int k = c + 1; k < 7; ++k) v -= M[c][k] * B[n][k];
-      B[n][c] = v * inv;
-    }
-  }
-}
-
-// w0 + R d for the characteristic offset d
-__device__ __forceinline__ void char_back(const double* w0, double bn, double gamma, const double* d, double* out) {
-  double R[7][7];
-  char_right(w0, bn, gamma, R);
-#pragma unroll
-  for (int j = 0; j < 7; ++j) {
-    double v = 0.0;
-#pragma unroll
-    for (int k = 0; k < 7; ++k) v += R[j][k] * d[k];
-    out[j] = w0[j] + v;
-  }
-}
-
-// PLM edges of cell w0 on characteristic variables: the one-sided differences
-// projected with L, van Leer-limited per wave family, projected back with R.
-__device__ void char_plm(const double* wm, const double* w0, const double* wp, double bn, double gamma,
-                         double* left, double* right) {
-  double B[2][7];
-#pragma unroll
-  for (int r = 0; r < 7; ++r) {
-    B[0][r] = w0[r] - wm[r];
-    B[1][r] = wp[r] - w0[r];
-  }
-  char_project<2>(w0, bn, gamma, B);
-  double dl[7], dr[7];
-#pragma unroll
-  for (int k = 0; k < 7; ++k) {
-    const double pr = B[0][k] * B[1][k];
-    const double dc = pr > 0.0 ? 2.0 * pr / (B[0][k] + B[1][k]) : 0.0;
-    dl[k] = -0.5 * dc;
-    dr[k] = 0.5 * dc;
-  }
-  char_back(w0, bn, gamma, dl, left);
-  char_back(w0, bn, gamma, dr, right);
-}
-
-// PPM edges of the middle cell of the stencil st[0..4] on characteristic
-// variables: the differences from the middle cell projected with L, the
-// limited parabola per wave family, the edge offsets projected back with R.
-__device__ void char_ppm(const double (&st)[5][7], double bn, double gamma, double* left, double* right) {
-  double B[4][7];
-#pragma unroll
-  for (int r = 0; r < 7; ++r) {
-    B[0][r] = st[0][r] - st[2][r];
-    B[1][r] = st[1][r] - st[2][r];
-    B[2][r] = st[3][r] - st[2][r];
-    B[3][r] = st[4][r] - st[2][r];
-  }
-  char_project<4>(st[2], bn, gamma, B);
-  double cl[7], cr[7];
-#pragma unroll
-  for (int k = 0; k < 7; ++k) {
-    const double q[5] = {B[0][k], B[1][k], 0.0, B[2][k], B[3][k]};
-    cell_edges<2>(q, cl[k], cr[k]);
-  }
-  char_back(st[2], bn, gamma, cl, left);
-  char_back(st[2], bn, gamma, cr, right);
-}
-
 // Fluxes through the faces normal to D: normal index [ng, ng+n_D], transverse
 // indices [ng-1, ng+n_t] (one extra ring for the corner EMFs).  CHAR: PLM or
 // PPM on characteristic variables.
@@ -260,42 +91,24 @@ __global__ void __launch_bounds__(kThreads) k_flux(Geo g, Gas gas, double ct_eps
   const int s = D == 0 ? 1 : (D == 1 ? g.N1 : g.N1 * g.N2);
   const int q = g.c(i, j, k);
   FaceState L, R;
-  if (CHAR && RECON == 1) {
-    // cells c-2 .. c+1 in the face frame; right edge of c-1, left edge of c
+  if constexpr (CHAR && RECON > 0) {
+    // right edge of cell c-1, left edge of cell c, in the face frame
+    constexpr int NW = 2 * RECON + 1;
     const int vi[7] = {0, 1 + D, 1 + T1, 1 + T2, 4, 5 + T1, 5 + T2};
-    double w[4][7];
+    double lr[2][7];
 #pragma unroll
-    for (int o = 0; o < 4; ++o)
+    for (int side = 0; side < 2; ++side) {
+      const int qc = q + (side - 1) * s;
+      double line[NW][7];
 #pragma unroll
-      for (int n = 0; n < 7; ++n) w[o][n] = wb[vi[n] * g.cvar + q + (o - 2) * s];
-    const double bnm = wb[(5 + D) * g.cvar + q - s], bn0 = wb[(5 + D) * g.cvar + q];
-    double lm[7], rm[7], l0[7], r0[7];
-    char_plm(w[0], w[1], w[2], bnm, gas.gamma, lm, rm);
-    char_plm(w[1], w[2], w[3], bn0, gas.gamma, l0, r0);
-    L = FaceState{rm[0], rm[1], rm[2], rm[3], rm[4], rm[5], rm[6]};
-    R = FaceState{l0[0], l0[1], l0[2], l0[3], l0[4], l0[5], l0[6]};
-  } else if (CHAR && RECON == 2) {
-    // cells c-3 .. c+2; right edge of c-1 (stencil c-3 .. c+1), left edge of c
-    const int vi[7] = {0, 1 + D, 1 + T1, 1 + T2, 4, 5 + T1, 5 + T2};
-    double lm[7], rm[7], l0[7], r0[7];
-    {
-      double st[5][7];
+      for (int o = 0; o < NW; ++o)
 #pragma unroll
-      for (int o = 0; o < 5; ++o)
-#pragma unroll
-        for (int n = 0; n < 7; ++n) st[o][n] = wb[vi[n] * g.cvar + q + (o - 3) * s];
-      char_ppm(st, wb[(5 + D) * g.cvar + q - s], gas.gamma, lm, rm);
+        for (int n = 0; n < 7; ++n) line[o][n] = wb[vi[n] * g.cvar + qc + (o - RECON) * s];
+      char_edges<RECON>(line, wb[(5 + D) * g.cvar + qc], gas.gamma, side == 1 ? lr[1] : nullptr,
+                        side == 0 ? lr[0] : nullptr);
     }
-    {
-      double st[5][7];
-#pragma unroll
-      for (int o = 0; o < 5; ++o)
-#pragma unroll
-        for (int n = 0; n < 7; ++n) st[o][n] = wb[vi[n] * g.cvar + q + (o - 2) * s];
-      char_ppm(st, wb[(5 + D) * g.cvar + q], gas.gamma, l0, r0);
-    }
-    L = FaceState{rm[0], rm[1], rm[2], rm[3], rm[4], rm[5], rm[6]};
-    R = FaceState{l0[0], l0[1], l0[2], l0[3], l0[4], l0[5], l0[6]};
+    L = FaceState{lr[0][0], lr[0][1], lr[0][2], lr[0][3], lr[0][4], lr[0][5], lr[0][6]};
+    R = FaceState{lr[1][0], lr[1][1], lr[1][2], lr[1][3], lr[1][4], lr[1][5], lr[1][6]};
   } else {
     recon_pair<RECON>(wb + q, s, L.rho, R.rho);
     recon_pair<RECON>(wb + (1 + D) * g.cvar + q, s, L.vn, R.vn);

@@ -515,6 +515,128 @@ __device__ __forceinline__ void cell_edges(const double* s, double& left, double
   }
 }
 
+// ---- characteristic reconstruction (Sec. 3.2.1: C = L W) -------------------
+// Face frame, primitives w = (rho, vn, vt1, vt2, P, Bt1, Bt2), normal field bn.
+// The right eigenvectors of W_t + A W_x = 0 for the waves vn -+ cf, vn -+ cs,
+// vn -+ ca, vn, normalised after Roe & Balsara (1996): alpha_f, alpha_s from
+// the fast and slow speeds (1, 0 where they are equal), beta along the
+// transverse field (1/sqrt2 each where it vanishes), so they stay independent
+// where speeds coincide.
+// The split of dW into waves is solved by hand.  With the transverse parts
+// along and across the field direction, the sums fs, ss of the fast and the
+// slow pair and their differences fd, sd (right- minus left-going) meet
+//   dP = gamma P (af fs + as ss),  dB_par = sqrt(rho) a (as fs - af ss),
+//   du = af cf fd + as cs sd,      dv_par = sg (af cf sd - as cs fd),
+// two 2 x 2 systems (af^2 + as^2 = 1); the Alfven pair carries the parts across
+// the field, the entropy wave the rest of d rho.
+struct CharBasis {
+  double rho, af, as, ff, ss, iq;     // ff = af cf, ss = as cs, iq = 1 / (ff^2 + ss^2)
+  double e1, e2, sg, sr, isr, sra, isra, gp, igp;  // sr = sqrt(rho), sra = sr a, gp = gamma P
+};
+
+__device__ __forceinline__ CharBasis char_basis(const double* w, double bn, double gamma) {
+  CharBasis c;
+  const double rho = w[0], t1 = w[5], t2 = w[6], bt2 = t1 * t1 + t2 * t2;
+  c.rho = rho;
+  c.gp = gamma * w[4];
+  c.igp = frcp(c.gp);
+  c.isr = frsq(rho);
+  c.sr = rho * c.isr;
+  const double ir = c.isr * c.isr;
+  const double a2 = c.gp * ir, ca2 = bn * bn * ir, sum = a2 + ca2 + bt2 * ir;
+  const double disc = fmax(sum * sum - 4.0 * a2 * ca2, 0.0);
+  const double cf2 = 0.5 * (sum + fsqrt(disc));
+  const double cs2 = cf2 > 0.0 ? a2 * ca2 * frcp(cf2) : 0.0;
+  const double d = cf2 - cs2;
+  const bool split = d > 0.0;
+  const double id = frcp(split ? d : 1.0);
+  c.af = split ? fsqrt(fmin(1.0, fmax(0.0, (a2 - cs2) * id))) : 1.0;
+  c.as = split ? fsqrt(fmin(1.0, fmax(0.0, (cf2 - a2) * id))) : 0.0;
+  c.ff = c.af * fsqrt(cf2);
+  c.ss = c.as * fsqrt(cs2);
+  c.iq = frcp(c.ff * c.ff + c.ss * c.ss);
+  const bool field = bt2 > 0.0;
+  const double ib = frsq(field ? bt2 : 2.0);
+  c.e1 = (field ? t1 : 1.0) * ib;
+  c.e2 = (field ? t2 : 1.0) * ib;
+  c.sg = bn >= 0.0 ? 1.0 : -1.0;
+  const double a = fsqrt(a2);
+  c.sra = c.sr * a;
+  c.isra = frcp(c.sra);
+  return c;
+}
+
+// wave amplitudes of dw: fast -+, slow -+, Alfven -+, entropy
+__device__ __forceinline__ void char_split(const CharBasis& c, const double* dw, double* x) {
+  const double par = c.sg * (c.e1 * dw[2] + c.e2 * dw[3]), per = c.e2 * dw[2] - c.e1 * dw[3];
+  const double p = dw[4] * c.igp, b = (c.e1 * dw[5] + c.e2 * dw[6]) * c.isra;
+  const double al = (c.e1 * dw[6] - c.e2 * dw[5]) * (c.sg * c.isr);
+  const double fs = c.af * p + c.as * b, ss = c.as * p - c.af * b;
+  const double fd = (c.ff * dw[1] - c.ss * par) * c.iq, sd = (c.ss * dw[1] + c.ff * par) * c.iq;
+  x[0] = 0.5 * (fs - fd);
+  x[1] = 0.5 * (fs + fd);
+  x[2] = 0.5 * (ss - sd);
+  x[3] = 0.5 * (ss + sd);
+  x[4] = 0.5 * (al - per);
+  x[5] = 0.5 * (al + per);
+  x[6] = dw[0] - c.rho * p;
+}
+
+// the primitive difference of the wave amplitudes x
+__device__ __forceinline__ void char_join(const CharBasis& c, const double* x, double* dw) {
+  const double fs = x[0] + x[1], fd = x[1] - x[0], ss = x[2] + x[3], sd = x[3] - x[2];
+  const double al = (x[4] + x[5]) * (c.sg * c.sr), per = x[5] - x[4];
+  const double p = c.af * fs + c.as * ss, par = c.sg * (c.ff * sd - c.ss * fd);
+  const double b = c.sra * (c.as * fs - c.af * ss);
+  dw[0] = x[6] + c.rho * p;
+  dw[1] = c.ff * fd + c.ss * sd;
+  dw[2] = c.e1 * par + c.e2 * per;
+  dw[3] = c.e2 * par - c.e1 * per;
+  dw[4] = c.gp * p;
+  dw[5] = c.e1 * b - c.e2 * al;
+  dw[6] = c.e2 * b + c.e1 * al;
+}
+
+// Edges of the middle cell of a line of 2 RECON + 1 cells (line[o][v]) on
+// characteristic variables: the differences from it split into its waves,
+// each wave reconstructed (PLM: van Leer slope; PPM: limited parabola), the
+// edge offsets joined again.  left / right: NULL when not wanted.
+template <int RECON>
+__device__ __forceinline__ void char_edges(const double (&line)[2 * RECON + 1][7], double bn, double gamma, double* left,
+                                           double* right) {
+  const double* w = line[RECON];
+  const CharBasis c = char_basis(w, bn, gamma);
+  double x[2 * RECON][7];
+#pragma unroll
+  for (int o = 0; o < 2 * RECON; ++o) {
+    const double* q = line[o < RECON ? o : o + 1];
+    double dw[7];
+#pragma unroll
+    for (int v = 0; v < 7; ++v) dw[v] = q[v] - w[v];
+    char_split(c, dw, x[o]);
+  }
+  double lo[7], hi[7];
+#pragma unroll
+  for (int k = 0; k < 7; ++k) {
+    double q[2 * RECON + 1];
+#pragma unroll
+    for (int o = 0; o < 2 * RECON; ++o) q[o < RECON ? o : o + 1] = x[o][k];
+    q[RECON] = 0.0;
+    cell_edges<RECON>(q, lo[k], hi[k]);
+  }
+  double d[7];
+  if (left) {
+    char_join(c, lo, d);
+#pragma unroll
+    for (int v = 0; v < 7; ++v) left[v] = w[v] + d[v];
+  }
+  if (right) {
+    char_join(c, hi, d);
+#pragma unroll
+    for (int v = 0; v < 7; ++v) right[v] = w[v] + d[v];
+  }
+}
+
 // Upwind CT corner EMF (Gardiner & Stone 2005) at the edge shared by four
 // cells.  Notation for component e with transverse directions a, b:
 //   ea0 = face-a EMF at (c), ea1 = at (c - b)   [faces normal to a]

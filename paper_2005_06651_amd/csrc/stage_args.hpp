@@ -68,6 +68,9 @@ struct BatchArgs {
 // unit per (T, RECON) holds the kernels.
 template <int RECON, class T>
 hipError_t launch_uniform(int rs, const UniformArgs& a, hipStream_t s);
+// (launch_charac: PLM on characteristic variables, periodic blocks)
+template <class T>
+hipError_t launch_charac(int rs, const UniformArgs& a, hipStream_t s);
 template <class T, int RECON>
 hipError_t launch_batch(int rs, const BatchArgs& a, int grid, hipStream_t s, bool mesh);
 

@@ -266,7 +266,13 @@ __device__ __forceinline__ void face_update(const Geo& g, const double* __restri
 // SAME (donor cell only): the stage input is U^n itself (the first stage of
 // every scheme), so the output's pointwise terms come from the raw cell read
 // for the window one plane earlier, carried, instead of being read again.
-template <int RECON, int RS, class T, bool FL, bool MESH = false, bool MF = false, bool SAME = false>
+// CHAR: PLM on characteristic variables.  Every face takes the edges of its two
+// cells from their own waves (about 320 operations a cell, no face shares one
+// with its neighbour through LDS, which is full), 58 registers spilled; the
+// five-kernel pipeline with 7 x 7 eliminations it replaces took 5.97 ms per
+// VL2+HLLD step at 192^3, of which the donor-cell predictor 1.6 ms; now 1.97 ms.
+template <int RECON, int RS, class T, bool FL, bool MESH = false, bool MF = false, bool SAME = false,
+          bool CHAR = false>
 __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, const StageArgs& sa, int tile_x,
                                            int tile_y, int k0, int kend, double* __restrict__ sp,
                                            double* __restrict__ sx, double* __restrict__ sc) {
@@ -430,6 +436,19 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
     double wz = 0.5, e1z = 0.0, e2z = 0.0;
     {
       double zl[7], zr[7];
+      if constexpr (CHAR) {
+        double line[NW][7], right[7];
+#pragma unroll
+        for (int o = 0; o < NW; ++o)
+#pragma unroll
+          for (int v = 0; v < 7; ++v) line[o][v] = win[o].q[v];
+        char_edges<RECON>(line, win[LA].b3, sa.gas.gamma, zr, right);
+#pragma unroll
+        for (int v = 0; v < 7; ++v) {
+          zl[v] = qz_carry[v];
+          qz_carry[v] = right[v];
+        }
+      } else {
 #pragma unroll
       for (int v = 0; v < 7; ++v) {
         double line[NW];
@@ -440,6 +459,7 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
         zl[v] = qz_carry[v];
         zr[v] = left;
         qz_carry[v] = right;
+      }
       }
       if (zface) {
         const double bn3 = bnq[0][2];
@@ -492,6 +512,18 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
         const int row = (ty + LA) * PW + tx + LA;
         // x-frame order: rho, v1, v2, v3, P, B2, B3
         const int map[7] = {0, 1, 2, 3, 4, 6, 7};
+        if constexpr (CHAR) {
+#pragma unroll
+          for (int side = 0; side < 2; ++side) {
+            double line[NW][7];
+#pragma unroll
+            for (int o = 0; o < NW; ++o)
+#pragma unroll
+              for (int v = 0; v < 7; ++v) line[o][v] = sp[map[v] * PL + row + (o - LA - 1 + side)];
+            char_edges<RECON>(line, sp[5 * PL + row + (side - 1)], sa.gas.gamma, side == 1 ? qr : nullptr,
+                              side == 0 ? ql : nullptr);
+          }
+        } else {
 #pragma unroll
         for (int v = 0; v < 7; ++v) {
           const double* s = sp + map[v] * PL + row;
@@ -506,6 +538,7 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
           cell_edges<RECON>(lineR, b0, b1);
           ql[v] = a1;
           qr[v] = b0;
+        }
         }
         const double bn1 = bnq[0][0];
         FaceFlux fx;
@@ -534,6 +567,18 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
         const int col = (ty + LA) * PW + tx + LA;
         // y-frame order: rho, v2, v3, v1, P, B3, B1
         const int map[7] = {0, 2, 3, 1, 4, 7, 5};
+        if constexpr (CHAR) {
+#pragma unroll
+          for (int side = 0; side < 2; ++side) {
+            double line[NW][7];
+#pragma unroll
+            for (int o = 0; o < NW; ++o)
+#pragma unroll
+              for (int v = 0; v < 7; ++v) line[o][v] = sp[map[v] * PL + col + (o - LA - 1 + side) * PW];
+            char_edges<RECON>(line, sp[6 * PL + col + (side - 1) * PW], sa.gas.gamma, side == 1 ? qr : nullptr,
+                              side == 0 ? ql : nullptr);
+          }
+        } else {
 #pragma unroll
         for (int v = 0; v < 7; ++v) {
           const double* s = sp + map[v] * PL + col;
@@ -548,6 +593,7 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
           cell_edges<RECON>(lineR, b0, b1);
           ql[v] = a1;
           qr[v] = b0;
+        }
         }
         const double bn2 = bnq[0][1];
         FaceFlux fy;
@@ -680,7 +726,7 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
 // Uniform blocks: one workgroup per (tile, x3 segment, block), XCD-aware:
 // consecutive logical tiles land on the same XCD so that halo overlap hits its
 // L2.
-template <int RECON, int RS, class T, bool FL, bool MESH, bool MF, bool SAME = false>
+template <int RECON, int RS, class T, bool FL, bool MESH, bool MF, bool SAME = false, bool CHAR = false>
 __global__ void __launch_bounds__(T::NT) __attribute__((amdgpu_waves_per_eu(2)))
 k_stage_fused(UniformArgs a) {
   using S = Smem<RECON, T>;
@@ -701,7 +747,7 @@ k_stage_fused(UniformArgs a) {
                MF ? a.fm + blk * 3 * g.fvar : nullptr};
   const int k0 = g.ng + seg * a.kz;
   const int kend = min(k0 + a.kz, g.ng + g.n3);
-  stage_tile<RECON, RS, T, FL, MESH, MF, SAME>(g, bp, a.sa, tile_x, tile_y, k0, kend, sp, sx, sc);
+  stage_tile<RECON, RS, T, FL, MESH, MF, SAME, CHAR>(g, bp, a.sa, tile_x, tile_y, k0, kend, sp, sx, sc);
 }
 
 // Batched blocks of uneven sizes: a persistent grid whose workgroups pull
@@ -757,6 +803,14 @@ hipError_t uniform_rs(int rs, const UniformArgs& fa, hipStream_t s) {
   return uniform_fl<RECON, 0, T, MESH, MF>(fa, s);
 }
 
+template <int RS, class T>
+hipError_t charac_fl(const UniformArgs& fa, hipStream_t s) {
+  const dim3 grid((unsigned)(8 * fa.per_xcd)), wg(T::NT);
+  if (fa.sa.fl.on()) hipLaunchKernelGGL((k_stage_fused<1, RS, T, true, false, false, false, true>), grid, wg, 0, s, fa);
+  else hipLaunchKernelGGL((k_stage_fused<1, RS, T, false, false, false, false, true>), grid, wg, 0, s, fa);
+  return hipGetLastError();
+}
+
 template <class T, int RECON, int RS, bool MF, bool SAME>
 hipError_t batch_fl(const BatchArgs& ba, int grid, hipStream_t s) {
   if (ba.sa.fl.on())
@@ -782,6 +836,13 @@ hipError_t launch_uniform(int rs, const UniformArgs& fa, hipStream_t s) {
   if (fa.fm)
     return fa.g.mesh[0] ? uniform_rs<RECON, T, true, true>(rs, fa, s) : uniform_rs<RECON, T, false, true>(rs, fa, s);
   return fa.g.mesh[0] ? uniform_rs<RECON, T, true, false>(rs, fa, s) : uniform_rs<RECON, T, false, false>(rs, fa, s);
+}
+
+template <class T>
+hipError_t launch_charac(int rs, const UniformArgs& fa, hipStream_t s) {
+  if (rs == 1) return charac_fl<1, T>(fa, s);
+  if (rs == 2) return charac_fl<2, T>(fa, s);
+  return charac_fl<0, T>(fa, s);
 }
 
 template <class T, int RECON>
