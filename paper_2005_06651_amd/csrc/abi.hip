@@ -64,7 +64,8 @@ struct athmhd_s {
   WorkItem* d_sitems = nullptr;  // batched blocks: the scalar kernel's work items
   int nsitems = 0;
   int min_edge = 0;  // batched blocks: fewest active cells along any direction of any block
-  unsigned long long* d_dtmin = nullptr;  // running min of dx/(|v|+cf), bit pattern
+  unsigned long long* d_dtmin = nullptr;  // running min of dx/(|v|+cf), bit pattern; +inf between reductions
+  unsigned* d_dtcount = nullptr;          // workgroups done of a reduction (CflEnd), zero between reductions
   int* d_bad = nullptr;                   // counters of add_floor_count: [0] non-physical cells, [2, 4) floors (64-bit)
   Floors floors{0.0, 0.0};                // optional primitive floors (off by default)
   double* d_dtval = nullptr;              // dt of the step on the device (graph replay)
@@ -130,25 +131,15 @@ Scheme scheme_of(int integ) {
   }
 }
 
-// clear_bad: bit 0 clears the non-physical counter, bit 1 the floor counter
-__global__ void k_set_u64(unsigned long long* p, unsigned long long v, int* bad, int clear_bad) {
+// The counters of a handle at rest: bit 0 of clear clears the non-physical
+// count, bit 1 the floor count, bit 2 resets the CFL reduction
+__global__ void k_clear(unsigned long long* dt_bits, unsigned* count, int* bad, int clear) {
   if (threadIdx.x == 0 && blockIdx.x == 0) {
-    *p = v;
-    if (clear_bad & 1) bad[0] = 0;
-    if (clear_bad & 2) *reinterpret_cast<unsigned long long*>(bad + 2) = 0ull;
-  }
-}
-
-// End of a chained step: the next step's dt from the CFL minimum (cfl times
-// +inf when no cell gave a limit), and the non-physical count handed over and
-// cleared when the caller asked for it.
-__global__ void k_chain_finish(const unsigned long long* bits, double cfl, int* bad, double* dt_dev,
-                               int32_t* nbad_dev) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    *dt_dev = cfl * __longlong_as_double((long long)*bits);
-    if (nbad_dev) {
-      *nbad_dev = bad[0];
-      bad[0] = 0;
+    if (clear & 1) bad[0] = 0;
+    if (clear & 2) *reinterpret_cast<unsigned long long*>(bad + 2) = 0ull;
+    if (clear & 4) {
+      *dt_bits = 0x7ff0000000000000ull;  // +inf
+      *count = 0u;
     }
   }
 }
@@ -246,6 +237,7 @@ void free_all(athmhd_t h) {
   if (h->d_fm) (void)hipFree(h->d_fm);
   if (h->d_sitems) (void)hipFree(h->d_sitems);
   if (h->d_dtmin) (void)hipFree(h->d_dtmin);
+  if (h->d_dtcount) (void)hipFree(h->d_dtcount);
   if (h->d_bad) (void)hipFree(h->d_bad);
   if (h->d_dtval) (void)hipFree(h->d_dtval);
   if (h->d_desc) (void)hipFree(h->d_desc);
@@ -261,6 +253,7 @@ void free_all(athmhd_t h) {
 // Small device buffers every handle has.
 bool alloc_common(athmhd_t h) {
   return hipMalloc(&h->d_dtmin, sizeof(unsigned long long)) == hipSuccess &&
+         hipMalloc(&h->d_dtcount, sizeof(unsigned)) == hipSuccess &&
          hipMalloc(&h->d_bad, 4 * sizeof(int)) == hipSuccess && hipMalloc(&h->d_dtval, sizeof(double)) == hipSuccess &&
          hipHostMalloc(&h->h_pinned, 16, hipHostMallocDefault) == hipSuccess;
 }
@@ -383,20 +376,24 @@ hipError_t levels_stage(athmhd_t h, int recon, const double* xc, const double* x
   return e;
 }
 
-// The CFL minimum of a state folded into bits (atomic minimum of the bit
-// patterns of non-negative doubles).  floor: the floors of the last stage
-// are applied in the same pass (uniform and mesh handles).
-hipError_t launch_cfl(athmhd_t h, const double* cons, const double* bface, int nblocks, unsigned long long* bits,
-                      hipStream_t s, bool floor = false) {
+// The CFL reduction of a state, finished by its last launch (end.dt,
+// end.nbad).  floor: the floors of the last stage are applied in the same pass
+// (uniform and mesh handles).
+hipError_t launch_cfl(athmhd_t h, const double* cons, const double* bface, int nblocks, CflEnd end, hipStream_t s,
+                      bool floor = false) {
+  end.count = h->d_dtcount;
+  end.cfl = h->cfg.cfl;
   if (h->levels) {
-    hipError_t e = launch_newdt(h->g, h->cfg.gamma, cons, bface, 1, bits, h->floors, h->d_bad, s);
+    hipError_t e =
+        launch_newdt(h->g, h->cfg.gamma, cons, bface, 1, h->d_dtmin, h->floors, h->d_bad, CflEnd{}, s);
     if (e != hipSuccess) return e;
-    return launch_newdt(h->gf, h->cfg.gamma, cons + h->g.cblock, bface + h->g.fblock, 8, bits, h->floors,
-                        h->d_bad, s);
+    return launch_newdt(h->gf, h->cfg.gamma, cons + h->g.cblock, bface + h->g.fblock, 8, h->d_dtmin, h->floors,
+                        h->d_bad, end, s);
   }
-  if (h->batch) return launch_newdt_batch(h->d_desc, h->nbatch, 0, h->cfg.gamma, cons, bface, bits, h->floors,
-                                          h->d_bad, s);
-  return launch_newdt(h->g, h->cfg.gamma, cons, bface, nblocks, bits, h->floors, h->d_bad, s, floor);
+  if (h->batch)
+    return launch_newdt_batch(h->d_desc, h->nbatch, h->cfg.gamma, cons, bface, h->d_dtmin, h->floors, h->d_bad, end,
+                              s);
+  return launch_newdt(h->g, h->cfg.gamma, cons, bface, nblocks, h->d_dtmin, h->floors, h->d_bad, end, s, floor);
 }
 
 // Plan of the fused stage kernel on nblocks uniform blocks, kept per
@@ -451,13 +448,13 @@ hipError_t fill_ghosts(athmhd_t h, double* cons, double* bface, int nblocks, hip
 // dt_dev != NULL the stage kernels read dt from the device.
 // stages != NULL (uniform handles): the inputs of stages 1..S-1 are written
 // there (S-1 states, each all blocks' cons then all blocks' bface) instead of
-// the library's registers.  dt_bits != NULL: the CFL minimum of the new
-// state is folded into it after the step.
+// the library's registers.  chain != NULL: a chained step; the CFL reduction
+// of the new state follows and ends as it says.
 int enqueue_step(athmhd_t h, double* cons, double* bface, double dt, const double* dt_dev, int nblocks,
-                 hipStream_t s, double* stages = nullptr, unsigned long long* dt_bits = nullptr) {
+                 hipStream_t s, double* stages = nullptr, const CflEnd* chain = nullptr) {
   // a chained step with floors on a uniform or mesh handle floors its last
   // stage's output in the CFL pass, which reads the whole state anyway
-  const bool floor_in_cfl = dt_bits && h->floors.on() && !h->batch && !h->levels;
+  const bool floor_in_cfl = chain && h->floors.on() && !h->batch && !h->levels;
   const Scheme sc = scheme_of(h->cfg.integrator);
   const double* xc = cons;
   const double* xb = bface;
@@ -488,7 +485,7 @@ int enqueue_step(athmhd_t h, double* cons, double* bface, double dt, const doubl
     const int depth = all_layers ? 0 : recon + 1;
     // a chained step on a coupled batch takes its input's shell entries as
     // current: every step ends with an exchange of its output
-    const bool current = h->coupled && dt_bits && st == 0;
+    const bool current = h->coupled && chain && st == 0;
     if ((exchange || all_layers) && !current &&
         (e = fill_ghosts(h, const_cast<double*>(xc), const_cast<double*>(xb), nblocks, s, depth)) != hipSuccess)
       return hip_fail(h, e, "fill_ghosts launch");
@@ -539,7 +536,7 @@ int enqueue_step(athmhd_t h, double* cons, double* bface, double dt, const doubl
   if (h->levels && (e = levels_ghosts(h, cons, bface, s)) != hipSuccess) return hip_fail(h, e, "level ghost launch");
   if (h->coupled && (e = fill_ghosts(h, cons, bface, nblocks, s)) != hipSuccess)
     return hip_fail(h, e, "batch exchange launch");
-  if (dt_bits && (e = launch_cfl(h, cons, bface, nblocks, dt_bits, s, floor_in_cfl)) != hipSuccess)
+  if (chain && (e = launch_cfl(h, cons, bface, nblocks, *chain, s, floor_in_cfl)) != hipSuccess)
     return hip_fail(h, e, "newdt launch");
   return ATHMHD_OK;
 }
@@ -708,7 +705,7 @@ int athmhd_create(const athmhd_config* cfg, int nblocks_max, athmhd_t* out) {
     p += 8 * h->g.fvar * nblocks_max;
   }
   h->scr.edge = p;
-  hipLaunchKernelGGL(k_set_u64, dim3(1), dim3(64), 0, nullptr, h->d_dtmin, 0ull, h->d_bad, 3);
+  hipLaunchKernelGGL(k_clear, dim3(1), dim3(64), 0, nullptr, h->d_dtmin, h->d_dtcount, h->d_bad, 7);
   e = hipDeviceSynchronize();
   if (e != hipSuccess) {
     free_all(h);
@@ -819,7 +816,8 @@ int athmhd_create_batch(const athmhd_config* base, const int32_t* dims, const do
   bool ok = hipMalloc(&h->reg[0], state * sizeof(double)) == hipSuccess &&
             hipMalloc(&h->reg[1], state * sizeof(double)) == hipSuccess &&
             hipMalloc(&h->d_desc, nblocks * sizeof(BatchDesc)) == hipSuccess &&
-            hipMalloc(&h->d_queue, sizeof(unsigned)) == hipSuccess && alloc_common(h) &&
+            hipMalloc(&h->d_queue, 2 * sizeof(unsigned)) == hipSuccess &&
+            hipMemset(h->d_queue, 0, 2 * sizeof(unsigned)) == hipSuccess && alloc_common(h) &&
             (base->nscalars == 0 || hipMalloc(&h->d_fm, h->ftot * sizeof(double)) == hipSuccess);
   if (!ok) {
     (void)hipGetLastError();
@@ -861,7 +859,7 @@ int athmhd_create_batch(const athmhd_config* base, const int32_t* dims, const do
     delete h;
     return fail(nullptr, rc, "%s", msg.c_str());
   }
-  hipLaunchKernelGGL(k_set_u64, dim3(1), dim3(64), 0, nullptr, h->d_dtmin, 0ull, h->d_bad, 3);
+  hipLaunchKernelGGL(k_clear, dim3(1), dim3(64), 0, nullptr, h->d_dtmin, h->d_dtcount, h->d_bad, 7);
   e = hipDeviceSynchronize();
   if (e != hipSuccess) {
     free_all(h);
@@ -1052,7 +1050,7 @@ int athmhd_batch_tune(athmhd_t h, const double* cons, const double* bface, void*
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   // the tuning launches may have counted non-physical cells of the scratch output
-  hipLaunchKernelGGL(k_set_u64, dim3(1), dim3(64), 0, s, h->d_dtmin, 0ull, h->d_bad, 3);
+  hipLaunchKernelGGL(k_clear, dim3(1), dim3(64), 0, s, h->d_dtmin, h->d_dtcount, h->d_bad, 3);
   if (rc != ATHMHD_OK) return rc;
   if ((rc = build_items(h, bs, bsp)) != ATHMHD_OK) return rc;
   if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_fail(h, e, "tune synchronise");
@@ -1079,7 +1077,7 @@ int athmhd_floor_count(athmhd_t h, long long* count, void* stream) {
   hipStream_t s = (hipStream_t)stream;
   char* hp = (char*)h->h_pinned;
   hipError_t e = hipMemcpyAsync(hp, h->d_bad + 2, 8, hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) hipLaunchKernelGGL(k_set_u64, dim3(1), dim3(64), 0, s, h->d_dtmin, 0ull, h->d_bad, 2);
+  if (e == hipSuccess) hipLaunchKernelGGL(k_clear, dim3(1), dim3(64), 0, s, h->d_dtmin, h->d_dtcount, h->d_bad, 2);
   if (e == hipSuccess) e = hipGetLastError();
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return hip_fail(h, e, "floor count");
@@ -1145,16 +1143,10 @@ int athmhd_step_chain(athmhd_t h, double* cons, double* bface, int nblocks, doub
   if (h->levels && h->floors.on()) return fail(h, ATHMHD_EUNSUP, "a two-level composite runs without floors");
   if (!dt_dev) return fail(h, ATHMHD_EINVAL, "NULL dt_dev");
   hipStream_t s = (hipStream_t)stream;
-  const double inf = INFINITY;
-  unsigned long long inf_bits;
-  std::memcpy(&inf_bits, &inf, 8);
-  hipLaunchKernelGGL(k_set_u64, dim3(1), dim3(64), 0, s, h->d_dtmin, inf_bits, h->d_bad, 0);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return hip_fail(h, e, "chain init launch");
-  if ((rc = enqueue_step(h, cons, bface, 0.0, dt_dev, nblocks, s, nullptr, h->d_dtmin)) != ATHMHD_OK) return rc;
-  hipLaunchKernelGGL(k_chain_finish, dim3(1), dim3(64), 0, s, h->d_dtmin, h->cfg.cfl, h->d_bad, dt_dev, nbad_dev);
-  e = hipGetLastError();
-  return e == hipSuccess ? ATHMHD_OK : hip_fail(h, e, "chain finish launch");
+  CflEnd end;
+  end.dt = dt_dev;
+  end.nbad = nbad_dev;
+  return enqueue_step(h, cons, bface, 0.0, dt_dev, nblocks, s, nullptr, &end);
 }
 
 int athmhd_step_vjp(athmhd_t h, const double* cons_n, const double* bface_n, double dt, const double* stages,
@@ -1369,40 +1361,19 @@ int athmhd_newdt(athmhd_t h, const double* cons, const double* bface, int nblock
   if (rc) return rc;
   if (!dt_host) return fail(h, ATHMHD_EINVAL, "NULL dt_host");
   hipStream_t s = (hipStream_t)stream;
-  const double inf = INFINITY;
-  unsigned long long inf_bits;
-  std::memcpy(&inf_bits, &inf, 8);
-  hipLaunchKernelGGL(k_set_u64, dim3(1), dim3(64), 0, s, h->d_dtmin, inf_bits, h->d_bad, 0);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return hip_fail(h, e, "newdt init launch");
-  if (h->levels) {
-    e = launch_newdt(h->g, h->cfg.gamma, cons, bface, 1, h->d_dtmin, h->floors, h->d_bad, s);
-    if (e == hipSuccess)
-      e = launch_newdt(h->gf, h->cfg.gamma, cons + h->g.cblock, bface + h->g.fblock, 8, h->d_dtmin, h->floors,
-                       h->d_bad, s);
-  } else {
-    e = h->batch ? launch_newdt_batch(h->d_desc, h->nbatch, 0, h->cfg.gamma, cons, bface, h->d_dtmin, h->floors,
-                                      h->d_bad, s)
-                 : launch_newdt(h->g, h->cfg.gamma, cons, bface, nblocks, h->d_dtmin, h->floors, h->d_bad, s);
-  }
-  if (e != hipSuccess) return hip_fail(h, e, "newdt launch");
+  // the reduction leaves dt and the count in the handle's pinned host words
   char* hp = (char*)h->h_pinned;
-  if ((e = hipMemcpyAsync(hp, h->d_dtmin, 8, hipMemcpyDeviceToHost, s)) != hipSuccess ||
-      (e = hipMemcpyAsync(hp + 8, h->d_bad, 4, hipMemcpyDeviceToHost, s)) != hipSuccess)
-    return hip_fail(h, e, "newdt copy");
+  CflEnd end;
+  end.dt = (double*)hp;
+  end.nbad = (int32_t*)(hp + 8);
+  hipError_t e = launch_cfl(h, cons, bface, nblocks, end, s);
+  if (e != hipSuccess) return hip_fail(h, e, "newdt launch");
   if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_fail(h, e, "newdt synchronise");
-  unsigned long long bits;
   int bad;
-  std::memcpy(&bits, hp, 8);
+  std::memcpy(dt_host, hp, 8);
   std::memcpy(&bad, hp + 8, 4);
-  double m;
-  std::memcpy(&m, &bits, 8);
-  *dt_host = h->cfg.cfl * m;
-  if (bad != 0) {
-    hipLaunchKernelGGL(k_set_u64, dim3(1), dim3(64), 0, s, h->d_dtmin, bits, h->d_bad, 1);
-    (void)hipStreamSynchronize(s);
+  if (bad != 0)
     return fail(h, ATHMHD_ENONPHYS, "%d non-physical cell evaluations (rho <= 0, P <= 0 or not finite)", bad);
-  }
   return ATHMHD_OK;
 }
 

@@ -39,9 +39,21 @@ hipError_t launch_prolong(const Geo& g, const int flo[3], const int clo[3], cons
 hipError_t launch_prim2cons(const Geo& g, double gamma, const double* prim, const double* bface, double* cons,
                             int nb, hipStream_t s);
 // dt_bits: device uint64 holding the bit pattern of the running minimum of
-// dx_d/(|v_d| + c_f) (initialise to +inf bits); bad: device int counter
+// dx_d/(|v_d| + c_f); bad: device int counter.  The last workgroup of a launch
+// with end.count set finishes the reduction: *end.dt = end.cfl times the
+// minimum (+inf when no cell gave one), dt_bits back to +inf, and with
+// end.nbad set the count handed over and cleared, so that no launch of its own
+// has to prepare or to end a reduction.  Between reductions dt_bits is +inf and
+// *end.count zero.  end.dt and end.nbad may be pinned host memory.
+struct CflEnd {
+  unsigned* count = nullptr;  // workgroups done (NULL: another launch goes on with the reduction)
+  double cfl = 0.0;
+  double* dt = nullptr;
+  int32_t* nbad = nullptr;
+};
 hipError_t launch_newdt(const Geo& g, double gamma, const double* cons, const double* bface, int nb,
-                        unsigned long long* dt_bits, const Floors& fl, int* bad, hipStream_t s, bool floor = false);
+                        unsigned long long* dt_bits, const Floors& fl, int* bad, const CflEnd& end, hipStream_t s,
+                        bool floor = false);
 // (floor: apply the floors of launch_floor_state to cons first, in the same
 // pass; floors must be on)
 
@@ -143,7 +155,8 @@ int batch_tile_count();                             // candidate thread tiles
 void batch_tile_shape(int shape, int* tx, int* ty);  // active columns of a candidate
 int batch_tile_threads(int shape);
 // One stage of all blocks in one persistent launch of `grid` workgroups that
-// drain the item queue.  dt_dev, if not NULL, supplies dt on the device
+// drain the item queue (queue[0], and in queue[1] the workgroups that found it
+// empty; both zero between launches, the last workgroup clears them).  dt_dev, if not NULL, supplies dt on the device
 // (bdt = beta * dt); otherwise coef.bdt is used.
 // mesh: the blocks tile one domain and read their (exchanged) ghost entries
 // instead of their own periodic images (then without floors and fm).
@@ -173,9 +186,9 @@ hipError_t launch_exchange_batch(const BatchDesc* desc, const int64_t* off, cons
                                  int nwork, double* cons, double* bface, hipStream_t s);
 hipError_t launch_prim2cons_batch(const BatchDesc* desc, int nblocks, int64_t max_cells, double gamma,
                                   const double* prim, const double* bface, double* cons, hipStream_t s);
-hipError_t launch_newdt_batch(const BatchDesc* desc, int nblocks, int64_t max_active, double gamma,
-                              const double* cons, const double* bface, unsigned long long* dt_bits,
-                              const Floors& fl, int* bad, hipStream_t s);
+hipError_t launch_newdt_batch(const BatchDesc* desc, int nblocks, double gamma, const double* cons,
+                              const double* bface, unsigned long long* dt_bits, const Floors& fl, int* bad,
+                              const CflEnd& end, hipStream_t s);
 
 hipError_t launch_copy(double* dst, const double* src, int64_t n, hipStream_t s);
 

@@ -110,10 +110,6 @@ int batch_tile_threads(int shape) {
   return (tx + 2) * (ty + 2);
 }
 
-__global__ void k_zero_u32(unsigned* p) {
-  if (threadIdx.x == 0) *p = 0u;
-}
-
 template <class T>
 static hipError_t launch_batch_recon(int recon, int rs, const BatchArgs& ba, int grid, hipStream_t s, bool mesh) {
   if (recon == 0) return launch_batch<T, 0>(rs, ba, grid, s, mesh);
@@ -127,9 +123,6 @@ hipError_t launch_stage_batch(int shape, double gamma, int recon, int rs, double
                               StageCoef coef, const double* dt_dev, double beta, int grid, Floors fl, int* bad,
                               double* fm, hipStream_t s, bool mesh) {
   if (mesh && (fl.on() || fm)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, s, queue);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
   BatchArgs ba;
   ba.desc = desc;
   ba.items = items;

@@ -53,7 +53,7 @@ struct BatchArgs {
   const BatchDesc* desc;
   const WorkItem* items;
   int nitems;
-  unsigned* queue;  // work counter, zero at launch
+  unsigned* queue;  // work counter and workgroups done, both zero at launch and after it
   StageArgs sa;
   const double* xc;
   const double* xb;

@@ -765,7 +765,14 @@ __global__ void __launch_bounds__(T::NT) __attribute__((amdgpu_waves_per_eu(2)))
     __syncthreads();
     const int it = __builtin_amdgcn_readfirstlane(s_item);
     __syncthreads();
-    if (it >= a.nitems) break;
+    if (it >= a.nitems) {
+      // the last workgroup to find the queue empty clears it for the next launch
+      if (threadIdx.x == 0 && atomicAdd(a.queue + 1, 1u) == gridDim.x - 1) {
+        atomicExch(a.queue, 0u);
+        atomicExch(a.queue + 1, 0u);
+      }
+      break;
+    }
     const WorkItem w = a.items[it];
     const BatchDesc& d = a.desc[w.block];
     BlockPtrs bp{a.xc + d.coff, a.xb + d.foff, a.unc + d.coff, a.unb + d.foff, a.oc + d.coff, a.ob + d.foff,
