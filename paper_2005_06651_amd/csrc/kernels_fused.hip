@@ -12,8 +12,8 @@ namespace athmhd {
 // workgroup of 8 waves per CU).  Two 18 x 14 workgroups of 4 waves share a CU:
 //   * with DC and PLM a full round of them costs as much as one of the larger
 //     tile (15.9 and 16.0 us per plane of a VL2 step), with PPM 0.95 of it, and
-//     0.85 when rounds follow each other, as their barriers then fall apart
-//     (RK3 at 256^3: 59.7 and 50.6 us per plane);
+//     0.9 when rounds follow each other, as their barriers then fall apart
+//     (RK3 at 256^3: 53.5 and 47.7 us per plane);
 //   * one workgroup alone on each CU takes 0.75 of a round (12 us);
 //   * the last, partial round overlaps the one before it: at least half a
 //     round, else its share of the CUs (2.75 rounds at 128^3 measured 2.79,
@@ -22,7 +22,7 @@ static double rounds_small(int64_t wgs, int cus, int recon) {
   const double r = (double)wgs / (2.0 * cus);
   const double full = std::floor(r), f = r - full;
   const double tail = f == 0.0 ? 0.0 : full == 0.0 ? (f <= 0.5 ? 0.75 : 1.0) : std::max(0.5, f);
-  return (full + tail) * (recon < 2 ? 1.0 : r < 4.0 ? 0.95 : 0.85);
+  return (full + tail) * (recon < 2 ? 1.0 : r < 4.0 ? 0.95 : 0.9);
 }
 
 // Thread tile and x3 segment length of a launch: the pair with the least
@@ -32,7 +32,8 @@ static double rounds_small(int64_t wgs, int cus, int recon) {
 // the rule before (34 x 15 only, kz in 4, 8, .. 32 or 64) and now, per step:
 // 64^3 VL2+PLM 98 -> 83 us, 96^3 252 -> 193 us, 192^3 1415 -> 1242 us, 32^3 RK3+PPM
 // 363 -> 150 us, 200x150x131 RK3+PPM+HLLE 3.4 -> 2.6 ms; 256^3 VL2+PLM stays on
-// 34 x 15 and 32 planes (2.75 ms; 18 x 14: 2.94), RK3+PPM 10.1 -> 9.5 ms.
+// 34 x 15 and 32 planes (2.75 ms; 18 x 14: 2.94); RK3+PPM runs on 18 x 14 (9.1
+// and 8.9 ms).
 FusedPlan fused_plan(const Geo& g, int recon, int nb, int cus, int kz_fixed) {
   FusedPlan best{false, 1};
   double cost = 1e300;

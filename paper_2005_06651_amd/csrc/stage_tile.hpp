@@ -18,7 +18,7 @@
 //     plane below is written out once its upper x3 fluxes / EMFs exist
 //     (2S stage update, Eq. (rk-2s)).
 // Two barriers per plane: after the primitives are in LDS, and after the face
-// results are.  The face-field update that reads a plane's corner EMFs runs
+// results are (and two more where cell edges are shared through LDS).  The face-field update that reads a plane's corner EMFs runs
 // after the next plane's first barrier, and the exchange slots read by the
 // corner EMFs are written after that barrier too, so no third barrier is
 // needed to keep one plane's reads apart from the next plane's writes.
@@ -258,6 +258,58 @@ __device__ __forceinline__ void face_update(const Geo& g, const double* __restri
   }
   bacc[5] = a5;
   bacc[6] = a6;
+}
+
+// Reconstructed states of a cell and a face along one direction of the primitive
+// plane (row: the cell, st: stride of the direction), in the face's frame (map;
+// nrm: slot of the cell-centred normal field).
+// own_edges: left and right edge of the own cell.
+template <int RECON>
+__device__ __forceinline__ void own_edges(const double* __restrict__ sp, int PL, int row, int st, const int (&map)[7],
+                                          double* lo, double* hi) {
+  constexpr int NW = 2 * RECON + 1;
+#pragma unroll
+  for (int v = 0; v < 7; ++v) {
+    double line[NW];
+#pragma unroll
+    for (int o = 0; o < NW; ++o) line[o] = sp[map[v] * PL + row + (o - RECON) * st];
+    cell_edges<RECON>(line, lo[v], hi[v]);
+  }
+}
+
+// face_states: right edge of the cell below and left edge of the own cell.
+template <int RECON, bool CHAR>
+__device__ __forceinline__ void face_states(const double* __restrict__ sp, int PL, int row, int st,
+                                            const int (&map)[7], int nrm, double gamma, double* ql, double* qr) {
+  constexpr int NW = 2 * RECON + 1;
+  if constexpr (CHAR) {
+#pragma unroll
+    for (int side = 0; side < 2; ++side) {
+      double line[NW][7];
+#pragma unroll
+      for (int o = 0; o < NW; ++o)
+#pragma unroll
+        for (int v = 0; v < 7; ++v) line[o][v] = sp[map[v] * PL + row + (o - RECON - 1 + side) * st];
+      char_edges<RECON>(line, sp[nrm * PL + row + (side - 1) * st], gamma, side == 1 ? qr : nullptr,
+                        side == 0 ? ql : nullptr);
+    }
+  } else {
+#pragma unroll
+    for (int v = 0; v < 7; ++v) {
+      const double* s = sp + map[v] * PL + row;
+      double lineL[NW], lineR[NW];
+#pragma unroll
+      for (int o = 0; o < NW; ++o) {
+        lineL[o] = s[(o - RECON - 1) * st];
+        lineR[o] = s[(o - RECON) * st];
+      }
+      double a0, a1, b0, b1;
+      cell_edges<RECON>(lineL, a0, a1);
+      cell_edges<RECON>(lineR, b0, b1);
+      ql[v] = a1;
+      qr[v] = b0;
+    }
+  }
 }
 
 // One tile (tile_x, tile_y) of a block over the active planes [k0, kend).
@@ -503,114 +555,84 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
       ka = plane_next<MESH>(g, ka);
       load_raw<MESH>(g, xc, xb, own, ka, pre);
     }
-    // ---- 6. Riemann problems on the lower x1-face and x2-face in plane p
-    double e2x = 0.0, wx = 0.5, e1y = 0.0, wy = 0.5;
-    {
-      double e3x = 0.0;
-      if (tx >= 1) {
-        double ql[7], qr[7];
-        const int row = (ty + LA) * PW + tx + LA;
-        // x-frame order: rho, v1, v2, v3, P, B2, B3
-        const int map[7] = {0, 1, 2, 3, 4, 6, 7};
-        if constexpr (CHAR) {
+    // ---- 6. Riemann problems on the lower x1-face and x2-face in plane p.
+    // EDGES (PPM, and PLM on the 4-wave tiles): every thread reconstructs its own cell along x1 and x2 once;
+    // the left edge is its own face's right state, the right edge goes to the
+    // next thread through the slots that the face's results take afterwards.
+    // Two more barriers a plane, for a quarter of the loop's instructions
+    // (6171 -> 4682): 200x150x131 RK3+PPM+HLLE 2.81 -> 2.37 ms per step, 512^3 blast
+    // 82.0 -> 77.5 ms.  With PLM a slope is cheap, and it pays only where the
+    // other workgroup of the CU fills the barriers: 1024 batched blocks 3.60 ->
+    // 3.49 ms, but 256^3 on the 8-wave tile 2.93 -> 2.96 ms, characteristic PLM at
+    // 192^3 (spills) 1.93 -> 1.98 ms.
+    constexpr bool EDGES = RECON >= 2 || (RECON == 1 && !CHAR && NT != TileU::NT);
+    const int row = (ty + LA) * PW + tx + LA;  // own cell in the primitive plane
+    // x-frame order: rho, v1, v2, v3, P, B2, B3; y-frame order: rho, v2, v3, v1, P, B3, B1
+    constexpr int mapx[7] = {0, 1, 2, 3, 4, 6, 7}, mapy[7] = {0, 2, 3, 1, 4, 7, 5};
+    constexpr int slotx[7] = {X_FX, X_FX + 1, X_FX + 2, X_FX + 3, X_FX + 4, X_E3X, X_WX};
+    constexpr int sloty[7] = {X_FY, X_FY + 1, X_FY + 2, X_FY + 3, X_FY + 4, X_E3Y, X_WY};
+    double xr[7], yr[7];  // right states of the own faces
+    if constexpr (EDGES) {
+      double hi[7];
+      own_edges<RECON>(sp, PL, row, 1, mapx, xr, hi);
 #pragma unroll
-          for (int side = 0; side < 2; ++side) {
-            double line[NW][7];
+      for (int v = 0; v < 7; ++v) sx[slotx[v] * NT + tid] = hi[v];
+      own_edges<RECON>(sp, PL, row, PW, mapy, yr, hi);
 #pragma unroll
-            for (int o = 0; o < NW; ++o)
-#pragma unroll
-              for (int v = 0; v < 7; ++v) line[o][v] = sp[map[v] * PL + row + (o - LA - 1 + side)];
-            char_edges<RECON>(line, sp[5 * PL + row + (side - 1)], sa.gas.gamma, side == 1 ? qr : nullptr,
-                              side == 0 ? ql : nullptr);
-          }
-        } else {
-#pragma unroll
-        for (int v = 0; v < 7; ++v) {
-          const double* s = sp + map[v] * PL + row;
-          double lineL[NW], lineR[NW];
-#pragma unroll
-          for (int o = 0; o < NW; ++o) {
-            lineL[o] = s[o - LA - 1];
-            lineR[o] = s[o - LA];
-          }
-          double a0, a1, b0, b1;
-          cell_edges<RECON>(lineL, a0, a1);
-          cell_edges<RECON>(lineR, b0, b1);
-          ql[v] = a1;
-          qr[v] = b0;
-        }
-        }
-        const double bn1 = bnq[0][0];
-        FaceFlux fx;
-        riemann<RS, FL>(ql, qr, bn1, sa.gas, sa.ct_eps, sa.fl, nfl, fx, wx);
-        if (MF && act && p >= k0 && p < kend) put(face_plane(g, bp.fm, 0, p), own.f, fx.rho);
-        sx[(X_FX + 0) * NT + tid] = fx.rho;
-        sx[(X_FX + 1) * NT + tid] = fx.mn;   // M1
-        sx[(X_FX + 2) * NT + tid] = fx.mt1;  // M2
-        sx[(X_FX + 3) * NT + tid] = fx.mt2;  // M3
-        sx[(X_FX + 4) * NT + tid] = fx.e;
-        // x1-face E3 = -F(B2), E2 = +F(B3)
-        e3x = -fx.bt1;
-        e2x = fx.bt2;
-      }
-      sx[X_E3X * NT + tid] = e3x;
-      sx[X_WX * NT + tid] = wx;
+      for (int v = 0; v < 7; ++v) sx[sloty[v] * NT + tid] = hi[v];
+      __syncthreads();
     }
+    double e2x = 0.0, wx = 0.5, e1y = 0.0, wy = 0.5, e3x = 0.0, e3y = 0.0;
+    FaceFlux fx{0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    if (tx >= 1) {
+      double ql[7];
+      if constexpr (EDGES) {
+#pragma unroll
+        for (int v = 0; v < 7; ++v) ql[v] = sx[slotx[v] * NT + tid - 1];
+      } else {
+        face_states<RECON, CHAR>(sp, PL, row, 1, mapx, 5, sa.gas.gamma, ql, xr);
+      }
+      riemann<RS, FL>(ql, xr, bnq[0][0], sa.gas, sa.ct_eps, sa.fl, nfl, fx, wx);
+      if (MF && act && p >= k0 && p < kend) put(face_plane(g, bp.fm, 0, p), own.f, fx.rho);
+      // x1-face E3 = -F(B2), E2 = +F(B3)
+      e3x = -fx.bt1;
+      e2x = fx.bt2;
+    }
+    double yl[7];
+    if constexpr (EDGES) {
+      if (ty >= 1) {
+#pragma unroll
+        for (int v = 0; v < 7; ++v) yl[v] = sx[sloty[v] * NT + tid - BX];
+      }
+      __syncthreads();  // every edge read: the slots take the results
+    }
+    sx[(X_FX + 0) * NT + tid] = fx.rho;
+    sx[(X_FX + 1) * NT + tid] = fx.mn;   // M1
+    sx[(X_FX + 2) * NT + tid] = fx.mt1;  // M2
+    sx[(X_FX + 3) * NT + tid] = fx.mt2;  // M3
+    sx[(X_FX + 4) * NT + tid] = fx.e;
+    sx[X_E3X * NT + tid] = e3x;
+    sx[X_WX * NT + tid] = wx;
     if (PF == 1) {
       ka = plane_next<MESH>(g, ka);
       load_raw<MESH>(g, xc, xb, own, ka, pre);
     }
-    {
-      double e3y = 0.0;
-      if (ty >= 1) {
-        double ql[7], qr[7];
-        const int col = (ty + LA) * PW + tx + LA;
-        // y-frame order: rho, v2, v3, v1, P, B3, B1
-        const int map[7] = {0, 2, 3, 1, 4, 7, 5};
-        if constexpr (CHAR) {
-#pragma unroll
-          for (int side = 0; side < 2; ++side) {
-            double line[NW][7];
-#pragma unroll
-            for (int o = 0; o < NW; ++o)
-#pragma unroll
-              for (int v = 0; v < 7; ++v) line[o][v] = sp[map[v] * PL + col + (o - LA - 1 + side) * PW];
-            char_edges<RECON>(line, sp[6 * PL + col + (side - 1) * PW], sa.gas.gamma, side == 1 ? qr : nullptr,
-                              side == 0 ? ql : nullptr);
-          }
-        } else {
-#pragma unroll
-        for (int v = 0; v < 7; ++v) {
-          const double* s = sp + map[v] * PL + col;
-          double lineL[NW], lineR[NW];
-#pragma unroll
-          for (int o = 0; o < NW; ++o) {
-            lineL[o] = s[(o - LA - 1) * PW];
-            lineR[o] = s[(o - LA) * PW];
-          }
-          double a0, a1, b0, b1;
-          cell_edges<RECON>(lineL, a0, a1);
-          cell_edges<RECON>(lineR, b0, b1);
-          ql[v] = a1;
-          qr[v] = b0;
-        }
-        }
-        const double bn2 = bnq[0][1];
-        FaceFlux fy;
-        riemann<RS, FL>(ql, qr, bn2, sa.gas, sa.ct_eps, sa.fl, nfl, fy, wy);
-        if (MF && act && p >= k0 && p < kend) put(face_plane(g, bp.fm, 1, p), own.f, fy.rho);
-        sx[(X_FY + 0) * NT + tid] = fy.rho;
-        sx[(X_FY + 1) * NT + tid] = fy.mt2;  // M1
-        sx[(X_FY + 2) * NT + tid] = fy.mn;   // M2
-        sx[(X_FY + 3) * NT + tid] = fy.mt1;  // M3
-        sx[(X_FY + 4) * NT + tid] = fy.e;
-        // x2-face E1 = -F(B3), E3 = +F(B1)
-        e1y = -fy.bt1;
-        e3y = fy.bt2;
-      }
-      sx[X_E3Y * NT + tid] = e3y;
-      sx[X_WY * NT + tid] = wy;
+    if (ty >= 1) {
+      if constexpr (!EDGES) face_states<RECON, CHAR>(sp, PL, row, PW, mapy, 6, sa.gas.gamma, yl, yr);
+      FaceFlux fy;
+      riemann<RS, FL>(yl, yr, bnq[0][1], sa.gas, sa.ct_eps, sa.fl, nfl, fy, wy);
+      if (MF && act && p >= k0 && p < kend) put(face_plane(g, bp.fm, 1, p), own.f, fy.rho);
+      sx[(X_FY + 0) * NT + tid] = fy.rho;
+      sx[(X_FY + 1) * NT + tid] = fy.mt2;  // M1
+      sx[(X_FY + 2) * NT + tid] = fy.mn;   // M2
+      sx[(X_FY + 3) * NT + tid] = fy.mt1;  // M3
+      sx[(X_FY + 4) * NT + tid] = fy.e;
+      // x2-face E1 = -F(B3), E3 = +F(B1)
+      e1y = -fy.bt1;
+      e3y = fy.bt2;
     }
+    sx[X_E3Y * NT + tid] = e3y;
+    sx[X_WY * NT + tid] = wy;
     if (PF == 2) {
       ka = plane_next<MESH>(g, ka);
       load_raw<MESH>(g, xc, xb, own, ka, pre);
