@@ -283,12 +283,15 @@ ATHMHD_API int athmhd_prim2cons_vjp(athmhd_t h, const double* prim, const double
  * and faces).  Block b = bx + nbx (by + nby bz) sits at (bx, by, bz); cons and
  * bface hold the nbx nby nbz blocks one after the other as for athmhd_create,
  * and nblocks in later calls must equal that count.
- *   - Before every stage the library fills each block's ghost cells and every
- *     face entry other than the lower faces of its active cells from the
- *     block that owns that position (device kernel); each face is therefore
- *     updated by exactly one block, and shared faces cannot drift apart.
- *     athmhd_step thus writes the ghost entries of its input; after it they
- *     hold the last stage's input (athmhd_fill_ghosts refreshes them).
+ *   - A block's ghost cells, and every face entry other than the lower faces
+ *     of its active cells, belong to the block that owns that position; each
+ *     face is updated by exactly one block, and shared faces cannot drift
+ *     apart.  The stage kernels run over the whole domain and read neighbours
+ *     in place; with passive scalars, or where a layer of blocks along x3 holds
+ *     4 GiB or more per array, the library exchanges the ghost entries before
+ *     every stage instead (device kernel).  Either way athmhd_step leaves the
+ *     ghost entries of its input that its first stage reaches filled
+ *     (athmhd_fill_ghosts refreshes them after it).
  *   - athmhd_newdt, athmhd_prim2cons and the floors read the upper faces of a
  *     block's boundary cells from the neighbouring block, so they do not
  *     depend on ghost entries.

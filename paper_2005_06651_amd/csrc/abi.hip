@@ -463,6 +463,7 @@ int enqueue_step(athmhd_t h, double* cons, double* bface, double dt, const doubl
   // and the blocks of a coupled mesh or batch read ghost entries, which are
   // filled (exchanged between the blocks) before each stage
   const bool exchange = h->mesh || h->coupled;
+  const bool in_place = h->mesh && mesh_domain(h->g);  // neighbours read in place
   const int64_t ncell = h->batch ? h->ctot : h->g.cblock * nblocks;
   const int64_t nface = h->batch ? h->ftot : h->g.fblock * nblocks;
   if (sc.nstage == 1) {
@@ -486,7 +487,9 @@ int enqueue_step(athmhd_t h, double* cons, double* bface, double dt, const doubl
     // a chained step on a coupled batch takes its input's shell entries as
     // current: every step ends with an exchange of its output
     const bool current = h->coupled && chain && st == 0;
-    if ((exchange || all_layers) && !current &&
+    // a mesh read in place still leaves the ghost entries of its input filled
+    const bool fill = all_layers || (exchange && !(in_place && st > 0));
+    if (fill && !current &&
         (e = fill_ghosts(h, const_cast<double*>(xc), const_cast<double*>(xb), nblocks, s, depth)) != hipSuccess)
       return hip_fail(h, e, "fill_ghosts launch");
     const bool last = st == sc.nstage - 1;

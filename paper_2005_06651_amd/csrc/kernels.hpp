@@ -113,6 +113,15 @@ hipError_t launch_level_fine_faces(const Geo& gf, const double* xb, const double
 // dt_dev, if not NULL, supplies dt on the device (bdt = beta * dt).
 // bad[0] counts threads that met a non-physical cell; floor activations go to
 // the 64-bit counter of add_floor_count.
+// Whether a stage on the blocks of a coupled mesh runs over its domain and
+// reads neighbours in place, without exchanged ghost entries: without passive
+// scalars (their kernel reads ghosts), and while a layer of blocks along x3
+// holds less than 4 GiB, the reach of the kernel's 32-bit offsets.
+inline bool mesh_domain(const Geo& g) {
+  if (g.mesh[0] <= 0 || g.ns > 0) return false;
+  const double layer = 8.0 * g.mesh[0] * g.mesh[1] * (double)(g.cblock > g.fblock ? g.cblock : g.fblock);
+  return layer < 4294967296.0;
+}
 struct FusedPlan {
   bool small;  // 18 x 14 threads per workgroup instead of 34 x 15
   int kz;      // x3 planes per workgroup

@@ -34,8 +34,15 @@ static double rounds_small(int64_t wgs, int cus, int recon) {
 // 363 -> 150 us, 200x150x131 RK3+PPM+HLLE 3.4 -> 2.6 ms; 256^3 VL2+PLM stays on
 // 34 x 15 and 32 planes (2.75 ms; 18 x 14: 2.94); RK3+PPM runs on 18 x 14 (9.1
 // and 8.9 ms).
-FusedPlan fused_plan(const Geo& g, int recon, int nb, int cus, int kz_fixed) {
+FusedPlan fused_plan(const Geo& geo, int recon, int nb, int cus, int kz_fixed) {
   FusedPlan best{false, 1};
+  Geo g = geo;
+  if (mesh_domain(geo)) {
+    g.n1 *= geo.mesh[0];
+    g.n2 *= geo.mesh[1];
+    g.n3 *= geo.mesh[2];
+    nb = 1;
+  }
   double cost = 1e300;
   const int64_t cols_u = (int64_t)((g.n1 + TileU::TX - 1) / TileU::TX) * ((g.n2 + TileU::TY - 1) / TileU::TY) * nb;
   const int64_t cols_s = (int64_t)((g.n1 + TileS::TX - 1) / TileS::TX) * ((g.n2 + TileS::TY - 1) / TileS::TY) * nb;
@@ -87,11 +94,14 @@ hipError_t launch_stage_fused(const Geo& g, double gamma, int recon, int rs, dou
   fa.xc = xc; fa.xb = xb; fa.unc = unc; fa.unb = unb; fa.oc = outc; fa.ob = outb;
   fa.fm = fm;
   fa.kz = plan.kz;
+  fa.domain = mesh_domain(g);
+  const int n1 = fa.domain ? g.mesh[0] * g.n1 : g.n1, n2 = fa.domain ? g.mesh[1] * g.n2 : g.n2;
+  const int n3 = fa.domain ? g.mesh[2] * g.n3 : g.n3;
   const int TX = plan.small ? TileS::TX : TileU::TX, TY = plan.small ? TileS::TY : TileU::TY;
-  fa.ntx = (g.n1 + TX - 1) / TX;
-  fa.nty = (g.n2 + TY - 1) / TY;
-  fa.nseg = (g.n3 + fa.kz - 1) / fa.kz;
-  fa.total = (int64_t)fa.ntx * fa.nty * fa.nseg * nb;
+  fa.ntx = (n1 + TX - 1) / TX;
+  fa.nty = (n2 + TY - 1) / TY;
+  fa.nseg = (n3 + fa.kz - 1) / fa.kz;
+  fa.total = (int64_t)fa.ntx * fa.nty * fa.nseg * (fa.domain ? 1 : nb);
   fa.per_xcd = (fa.total + 7) / 8;
   if (charac && recon == 1) return plan.small ? launch_charac<TileS>(rs, fa, s) : launch_charac<TileU>(rs, fa, s);
   return plan.small ? launch_uniform_recon<TileS>(recon, rs, fa, s) : launch_uniform_recon<TileU>(recon, rs, fa, s);

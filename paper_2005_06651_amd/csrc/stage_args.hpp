@@ -44,6 +44,7 @@ struct UniformArgs {
   double* oc;
   double* ob;
   double* fm;  // NULL, or the face mass-flux output of every block (3 face arrays per block)
+  bool domain;  // the tiles cover the domain of a coupled mesh (mesh_domain), not its blocks
   int ntx, nty, nseg, kz;
   int64_t total;    // workgroups doing work
   int64_t per_xcd;  // ceil(total / 8)

@@ -71,53 +71,84 @@ struct Raw {
   double b1lo, b1hi, b2lo, b2hi, b3lo, b3hi;
 };
 
-// Column of a block: byte offsets inside one x3 plane of its cell (a cell
-// array) and of its lower faces, its upper x1 face and its upper x2 face (a
-// face array).  A block that is its own periodic neighbour is read at the
-// periodic images directly, so its ghost entries are never needed; the blocks
-// of a coupled mesh read their ghost entries, which the mesh exchange fills
-// before every stage.
+// How a block's neighbours are read (MESH):
+//   0  the block is its own periodic neighbour: at the periodic images directly,
+//      so its ghost entries are never needed;
+//   1  the stored ghost entries, which an exchange filled before the stage
+//      (coupled batches, meshes with passive scalars);
+//   2  the blocks of a coupled mesh as one periodic domain: the tiles cover the
+//      domain, not the blocks, and every column and plane is read and written
+//      in the block that owns it, so no exchange is needed and tiles are not
+//      cut at block edges.
+// Column: byte offsets inside one x3 plane of its cell (a cell array) and of
+// its lower faces, its upper x1 face and its upper x2 face (a face array); with
+// MESH 2 they include the block's offset in its layer of blocks.
 // A plane's base address is the same for the whole workgroup (scalar
 // registers), so an access is one instruction with a 32-bit vector offset and
 // no vector address arithmetic.  A plane's offsets fit 32 bits: a face array
-// holds fewer than 2^31 entries in at least 6 planes.
+// holds fewer than 2^31 entries in at least 6 planes (MESH 2: checked when the
+// launch is chosen).
 struct Col {
   unsigned c, f, f1, f2;
 };
 
 // Stored index read for position idx (cell, or face when hi = N) along a
-// direction with n active cells: its periodic image when the block is its own
-// neighbour, else the stored entry itself (ghosts filled by the mesh
-// exchange), clamped into the array for the columns of a ragged tile past the
-// block edge, whose results are never written out.
-template <bool MESH>
+// direction with n active cells: its periodic image (MESH 0), or the stored
+// entry itself (MESH 1), clamped into the array for the columns of a ragged
+// tile past the block edge, whose results are never written out.
+template <int MESH>
 __device__ __forceinline__ int read_index(const Geo& g, int idx, int n, int hi) {
-  if (!MESH) return wrap_index(idx, n, g.ng);
+  if (MESH == 0) return wrap_index(idx, n, g.ng);
   return idx < 0 ? 0 : (idx > hi ? hi : idx);
 }
 
-// Plane cursor: the stored plane read for an unwrapped plane index (the index
-// itself, clamped where it is used, for the blocks of a coupled mesh), and
-// its successor.  Advancing it costs a compare, no division, in every plane.
-template <bool MESH>
-__device__ __forceinline__ int plane_at(const Geo& g, int k) {
-  return MESH ? k : wrap_index(k, g.n3, g.ng);
+// Plane cursor: the stored plane (and layer of blocks) read for an unwrapped
+// plane index, clamped where it is used with MESH 1.  Advancing it costs a
+// compare, no division, in every plane.
+struct Pos {
+  int k, b;
+};
+template <int MESH>
+__device__ __forceinline__ Pos pos_at(const Geo& g, int k) {
+  if (MESH == 0) return Pos{wrap_index(k, g.n3, g.ng), 0};
+  if (MESH == 1) return Pos{k, 0};
+  const int d = wrap_index(k, g.mesh[2] * g.n3, g.ng) - g.ng;
+  return Pos{g.ng + d % g.n3, d / g.n3};
 }
-template <bool MESH>
-__device__ __forceinline__ int plane_next(const Geo& g, int k) {
-  ++k;
-  return !MESH && k == g.ng + g.n3 ? g.ng : k;
+template <int MESH>
+__device__ __forceinline__ Pos pos_next(const Geo& g, Pos q) {
+  ++q.k;
+  if (MESH != 1 && q.k == g.ng + g.n3) {
+    q.k = g.ng;
+    if (MESH == 2) q.b = q.b + 1 == g.mesh[2] ? 0 : q.b + 1;
+  }
+  return q;
 }
-template <bool MESH>
-__device__ __forceinline__ int plane_read(int k, int hi) {
-  return MESH ? min(max(k, 0), hi) : k;
+template <int MESH>
+__device__ __forceinline__ Pos pos_read(Pos q, int hi) {
+  if (MESH == 1) q.k = min(max(q.k, 0), hi);
+  return q;
 }
 
-template <bool MESH>
+template <int MESH>
 __device__ __forceinline__ Col make_col(const Geo& g, int i, int j) {
+  Col c;
+  if (MESH == 2) {
+    const int D1 = g.mesh[0] * g.n1, D2 = g.mesh[1] * g.n2;
+    const int i0 = wrap_index(i, D1, g.ng) - g.ng, i1 = wrap_index(i + 1, D1, g.ng) - g.ng;
+    const int j0 = wrap_index(j, D2, g.ng) - g.ng, j1 = wrap_index(j + 1, D2, g.ng) - g.ng;
+    const int a0 = i0 / g.n1, a1 = i1 / g.n1, b0 = j0 / g.n2, b1 = j1 / g.n2;
+    const unsigned x0 = (unsigned)(g.ng + i0 - a0 * g.n1), x1 = (unsigned)(g.ng + i1 - a1 * g.n1);
+    const unsigned y0 = (unsigned)(g.ng + j0 - b0 * g.n2), y1 = (unsigned)(g.ng + j1 - b1 * g.n2);
+    const unsigned cb = (unsigned)g.cblock, fb = (unsigned)g.fblock, m0 = (unsigned)g.mesh[0];
+    c.c = 8u * ((a0 + m0 * b0) * cb + y0 * g.N1 + x0);
+    c.f = 8u * ((a0 + m0 * b0) * fb + y0 * g.F1 + x0);
+    c.f1 = 8u * ((a1 + m0 * b0) * fb + y0 * g.F1 + x1);
+    c.f2 = 8u * ((a0 + m0 * b1) * fb + y1 * g.F1 + x0);
+    return c;
+  }
   const int i0 = read_index<MESH>(g, i, g.n1, g.N1 - 1), i1 = read_index<MESH>(g, i + 1, g.n1, g.N1);
   const int j0 = read_index<MESH>(g, j, g.n2, g.N2 - 1), j1 = read_index<MESH>(g, j + 1, g.n2, g.N2);
-  Col c;
   c.c = 8u * (unsigned)(j0 * g.N1 + i0);
   c.f = 8u * (unsigned)(j0 * g.F1 + i0);
   c.f1 = 8u * (unsigned)(j0 * g.F1 + i1);
@@ -125,13 +156,19 @@ __device__ __forceinline__ Col make_col(const Geo& g, int i, int j) {
   return c;
 }
 
-// base addresses of plane k of cell array v and of face array d
+// base addresses of plane q of cell array v and of face array d
 typedef const char* Plane;
-__device__ __forceinline__ Plane cell_plane(const Geo& g, const double* x, int v, int k) {
-  return reinterpret_cast<const char*>(x + (v * g.cvar + (int64_t)k * (g.N1 * g.N2)));
+template <int MESH>
+__device__ __forceinline__ Plane cell_plane(const Geo& g, const double* x, int v, Pos q) {
+  int64_t o = v * g.cvar + (int64_t)q.k * (g.N1 * g.N2);
+  if (MESH == 2) o += q.b * (g.cblock * (g.mesh[0] * g.mesh[1]));
+  return reinterpret_cast<const char*>(x + o);
 }
-__device__ __forceinline__ Plane face_plane(const Geo& g, const double* x, int d, int k) {
-  return reinterpret_cast<const char*>(x + (d * g.fvar + (int64_t)k * (g.F1 * g.F2)));
+template <int MESH>
+__device__ __forceinline__ Plane face_plane(const Geo& g, const double* x, int d, Pos q) {
+  int64_t o = d * g.fvar + (int64_t)q.k * (g.F1 * g.F2);
+  if (MESH == 2) o += q.b * (g.fblock * (g.mesh[0] * g.mesh[1]));
+  return reinterpret_cast<const char*>(x + o);
 }
 __device__ __forceinline__ double at(Plane pl, unsigned off) { return *reinterpret_cast<const double*>(pl + off); }
 __device__ __forceinline__ void put(Plane pl, unsigned off, double v) {
@@ -151,20 +188,20 @@ __device__ __forceinline__ unsigned here(unsigned o) {
 
 // Conserved state and the six bounding face fields of the cell of column c in
 // the plane of cursor k.
-template <bool MESH>
-__device__ __forceinline__ void load_raw(const Geo& g, const double* xc, const double* xb, const Col& col, int k,
+template <int MESH>
+__device__ __forceinline__ void load_raw(const Geo& g, const double* xc, const double* xb, const Col& col, Pos k,
                                          Raw& r) {
   const Col c = here(col);
-  const int k0 = plane_read<MESH>(k, g.N3 - 1), k1 = plane_read<MESH>(plane_next<MESH>(g, k), g.N3);
+  const Pos k0 = pos_read<MESH>(k, g.N3 - 1), k1 = pos_read<MESH>(pos_next<MESH>(g, k), g.N3);
 #pragma unroll
-  for (int v = 0; v < 5; ++v) r.u[v] = at(cell_plane(g, xc, v, k0), c.c);
-  const Plane b1 = face_plane(g, xb, 0, k0), b2 = face_plane(g, xb, 1, k0);
+  for (int v = 0; v < 5; ++v) r.u[v] = at(cell_plane<MESH>(g, xc, v, k0), c.c);
+  const Plane b1 = face_plane<MESH>(g, xb, 0, k0), b2 = face_plane<MESH>(g, xb, 1, k0);
   r.b1lo = at(b1, c.f);
   r.b1hi = at(b1, c.f1);
   r.b2lo = at(b2, c.f);
   r.b2hi = at(b2, c.f2);
-  r.b3lo = at(face_plane(g, xb, 2, k0), c.f);
-  r.b3hi = at(face_plane(g, xb, 2, k1), c.f);
+  r.b3lo = at(face_plane<MESH>(g, xb, 2, k0), c.f);
+  r.b3hi = at(face_plane<MESH>(g, xb, 2, k1), c.f);
 }
 
 // cons -> prim: w = (rho, v1, v2, v3, P, B1cc, B2cc, B3cc); returns the flags
@@ -238,8 +275,10 @@ constexpr int exchange_slots() { return RECON >= 2 ? X_N - 1 : X_N; }
 // and B2 on the lower faces of cell q-1, writes B3 on the face q-1/2, and
 // leaves the partial B1, B2 of plane q in bacc[5], bacc[6].  pwb holds the
 // pointwise terms (g1 U^n + g0 X) of B1, B2 at q-1 and B3 at q.
+template <int MESH>
 __device__ __forceinline__ void face_update(const Geo& g, const double* __restrict__ sc, int tid, int BX, int NT,
-                                            unsigned f, int q, int k0, int kend, double i1, double i2, double i3,
+                                            unsigned f, int q, Pos at_q, Pos below, int k0, int kend, double i1,
+                                            double i2, double i3,
                                             double bdt, const double* pwb, double* bacc, double* ob) {
   const int tE = tid + 1, tN = tid + BX;
   const double e1 = sc[0 * NT + tid], e2 = sc[1 * NT + tid], e3 = sc[2 * NT + tid];
@@ -251,10 +290,10 @@ __device__ __forceinline__ void face_update(const Geo& g, const double* __restri
   bacc[6] -= e1 * i3;
   // B3(i, j, q-1/2): -(E2(i+1/2) - E2(i-1/2))/dx1 + (E1(j+1/2) - E1(j-1/2))/dx2
   const double db3 = -(sc[1 * NT + tE] - e2) * i1 + (sc[0 * NT + tN] - e1) * i2;
-  if (q < kend) put(face_plane(g, ob, 2, q), f, pwb[2] + bdt * db3);
+  if (q < kend) put(face_plane<MESH>(g, ob, 2, at_q), f, pwb[2] + bdt * db3);
   if (q - 1 >= k0) {
-    put(face_plane(g, ob, 0, q - 1), f, pwb[0] + bdt * bacc[5]);
-    put(face_plane(g, ob, 1, q - 1), f, pwb[1] + bdt * bacc[6]);
+    put(face_plane<MESH>(g, ob, 0, below), f, pwb[0] + bdt * bacc[5]);
+    put(face_plane<MESH>(g, ob, 1, below), f, pwb[1] + bdt * bacc[6]);
   }
   bacc[5] = a5;
   bacc[6] = a6;
@@ -323,8 +362,7 @@ __device__ __forceinline__ void face_states(const double* __restrict__ sp, int P
 // with its neighbour through LDS, which is full), 58 registers spilled; the
 // five-kernel pipeline with 7 x 7 eliminations it replaces took 5.97 ms per
 // VL2+HLLD step at 192^3, of which the donor-cell predictor 1.6 ms; now 1.97 ms.
-template <int RECON, int RS, class T, bool FL, bool MESH = false, bool MF = false, bool SAME = false,
-          bool CHAR = false>
+template <int RECON, int RS, class T, bool FL, int MESH = 0, bool MF = false, bool SAME = false, bool CHAR = false>
 __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, const StageArgs& sa, int tile_x,
                                            int tile_y, int k0, int kend, double* __restrict__ sp,
                                            double* __restrict__ sx, double* __restrict__ sc) {
@@ -348,7 +386,9 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
   // that are never written out); reads use the periodic images
   const int gi = x0 - 1 + tx, gj = y0 - 1 + ty;
   const Col own = make_col<MESH>(g, gi, gj);
-  const bool act = tx >= 1 && tx <= TX && ty >= 1 && ty <= TY && gi < g.ng + g.n1 && gj < g.ng + g.n2;
+  const bool act = tx >= 1 && tx <= TX && ty >= 1 && ty <= TY && 
+                   gi < g.ng + (MESH == 2 ? g.mesh[0] * g.n1 : g.n1) &&
+                   gj < g.ng + (MESH == 2 ? g.mesh[1] * g.n2 : g.n2);
 
   // ---- extra LDS rings (LA per side): left and right columns (BY cells per
   // depth), bottom and top rows (BX cells per depth), one cell per thread
@@ -387,14 +427,15 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
   constexpr bool RELOAD_BN = LA >= 2;
   constexpr int NBQ = RELOAD_BN ? 1 : LA + 1;
   double bnq[NBQ][3];
-  int ka = plane_at<MESH>(g, k0 - 1 - LA), kr = plane_at<MESH>(g, k0 - 1);  // next own and ring planes to load
+  // next own plane to load, and planes p, p - 1 and p - 2
+  Pos ka = pos_at<MESH>(g, k0 - 1 - LA), kr = pos_at<MESH>(g, k0 - 1), kr1 = kr, kr2 = kr;
   {
     double w[8];
     Raw raw;
 #pragma unroll
     for (int o = 0; o < NW - 1; ++o) {
       load_raw<MESH>(g, xc, xb, own, ka, raw);
-      ka = plane_next<MESH>(g, ka);
+      ka = pos_next<MESH>(g, ka);
       const int f = to_prim<FL>(raw, gm1, sa.fl, w);
       nbad += f & 1;
       nfl += f >> 1;
@@ -447,9 +488,9 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
         unext[6] = pre.b2lo;
       }
       if (RELOAD_BN) {
-        const int kp = plane_read<MESH>(kr, g.N3 - 1);
+        const Pos kp = pos_read<MESH>(kr, g.N3 - 1);
 #pragma unroll
-        for (int d = 0; d < 3; ++d) bnq[0][d] = at(face_plane(g, xb, d, kp), own.f);
+        for (int d = 0; d < 3; ++d) bnq[0][d] = at(face_plane<MESH>(g, xb, d, kp), own.f);
       } else {
         bnq[NBQ - 1][0] = pre.b1lo;
         bnq[NBQ - 1][1] = pre.b2lo;
@@ -521,7 +562,7 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
         fz_cons[0] = fz.rho; fz_cons[1] = fz.mt1; fz_cons[2] = fz.mt2; fz_cons[3] = fz.mn; fz_cons[4] = fz.e;
         e2z = -fz.bt1;
         e1z = fz.bt2;
-        if (MF && act && p < kend) put(face_plane(g, bp.fm, 2, p), own.f, fz.rho);
+        if (MF && act && p < kend) put(face_plane<MESH>(g, bp.fm, 2, kr), own.f, fz.rho);
       }
     }
     if (ring) {
@@ -549,10 +590,10 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
     // ---- 8, for plane p-1: its face-field updates from the corner EMFs that
     // the previous iteration left in sc
     if (act && p - 1 >= k0)
-      face_update(g, sc, tid, BX, NT, own.f, p - 1, k0, kend, i1, i2, i3, bdt, pwb, acc_prev, ob);
+      face_update<MESH>(g, sc, tid, BX, NT, own.f, p - 1, kr1, kr2, k0, kend, i1, i2, i3, bdt, pwb, acc_prev, ob);
 
     if (PF == 0) {
-      ka = plane_next<MESH>(g, ka);
+      ka = pos_next<MESH>(g, ka);
       load_raw<MESH>(g, xc, xb, own, ka, pre);
     }
     // ---- 6. Riemann problems on the lower x1-face and x2-face in plane p.
@@ -593,7 +634,7 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
         face_states<RECON, CHAR>(sp, PL, row, 1, mapx, 5, sa.gas.gamma, ql, xr);
       }
       riemann<RS, FL>(ql, xr, bnq[0][0], sa.gas, sa.ct_eps, sa.fl, nfl, fx, wx);
-      if (MF && act && p >= k0 && p < kend) put(face_plane(g, bp.fm, 0, p), own.f, fx.rho);
+      if (MF && act && p >= k0 && p < kend) put(face_plane<MESH>(g, bp.fm, 0, kr), own.f, fx.rho);
       // x1-face E3 = -F(B2), E2 = +F(B3)
       e3x = -fx.bt1;
       e2x = fx.bt2;
@@ -614,14 +655,14 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
     sx[X_E3X * NT + tid] = e3x;
     sx[X_WX * NT + tid] = wx;
     if (PF == 1) {
-      ka = plane_next<MESH>(g, ka);
+      ka = pos_next<MESH>(g, ka);
       load_raw<MESH>(g, xc, xb, own, ka, pre);
     }
     if (ty >= 1) {
       if constexpr (!EDGES) face_states<RECON, CHAR>(sp, PL, row, PW, mapy, 6, sa.gas.gamma, yl, yr);
       FaceFlux fy;
       riemann<RS, FL>(yl, yr, bnq[0][1], sa.gas, sa.ct_eps, sa.fl, nfl, fy, wy);
-      if (MF && act && p >= k0 && p < kend) put(face_plane(g, bp.fm, 1, p), own.f, fy.rho);
+      if (MF && act && p >= k0 && p < kend) put(face_plane<MESH>(g, bp.fm, 1, kr), own.f, fy.rho);
       sx[(X_FY + 0) * NT + tid] = fy.rho;
       sx[(X_FY + 1) * NT + tid] = fy.mt2;  // M1
       sx[(X_FY + 2) * NT + tid] = fy.mn;   // M2
@@ -634,7 +675,7 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
     sx[X_E3Y * NT + tid] = e3y;
     sx[X_WY * NT + tid] = wy;
     if (PF == 2) {
-      ka = plane_next<MESH>(g, ka);
+      ka = pos_next<MESH>(g, ka);
       load_raw<MESH>(g, xc, xb, own, ka, pre);
     }
     // the stored terms of this iteration's output (U^n, and the stage input
@@ -644,17 +685,18 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
     const bool out_cell = act && zface && p - 1 >= k0;
     double un[8], xg[8];
     if constexpr (!SAME) {
-      const int qc = max(p - 1, k0), qf = min(max(p, k0), kend - 1);
+      const Pos first = pos_at<MESH>(g, k0);
+      const Pos qc = p > k0 ? kr1 : first, qf = p < k0 ? first : (p < kend ? kr : kr1);
       const Col c = here(own);
 #pragma unroll
-      for (int v = 0; v < 5; ++v) un[v] = at(cell_plane(g, unc, v, qc), c.c);
+      for (int v = 0; v < 5; ++v) un[v] = at(cell_plane<MESH>(g, unc, v, qc), c.c);
 #pragma unroll
-      for (int d = 0; d < 3; ++d) un[5 + d] = at(face_plane(g, unb, d, d < 2 ? qc : qf), c.f);
+      for (int d = 0; d < 3; ++d) un[5 + d] = at(face_plane<MESH>(g, unb, d, d < 2 ? qc : qf), c.f);
       if (sa.cf.g0 != 0.0) {
 #pragma unroll
-        for (int v = 0; v < 5; ++v) xg[v] = at(cell_plane(g, xc, v, qc), c.c);
+        for (int v = 0; v < 5; ++v) xg[v] = at(cell_plane<MESH>(g, xc, v, qc), c.c);
 #pragma unroll
-        for (int d = 0; d < 3; ++d) xg[5 + d] = at(face_plane(g, xb, d, d < 2 ? qc : qf), c.f);
+        for (int d = 0; d < 3; ++d) xg[5 + d] = at(face_plane<MESH>(g, xb, d, d < 2 ? qc : qf), c.f);
       } else {
 #pragma unroll
         for (int v = 0; v < 8; ++v) xg[v] = 0.0;
@@ -710,7 +752,7 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
       }
       if (out_cell) {
 #pragma unroll
-        for (int v = 0; v < 5; ++v) put(cell_plane(g, oc, v, p - 1), own.c, pw[v] + bdt * acc_prev[v]);
+        for (int v = 0; v < 5; ++v) put(cell_plane<MESH>(g, oc, v, kr1), own.c, pw[v] + bdt * acc_prev[v]);
       }
 #pragma unroll
       for (int v = 0; v < 5; ++v) acc_prev[v] = acc[v];
@@ -736,11 +778,13 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
     sx[X_E1YP * NT + tid] = e1y;
     if constexpr (WY_REG) wy_prev = wy;
     else sx[X_WYP * NT + tid] = wy;
-    kr = plane_next<MESH>(g, kr);
+    kr2 = kr1;
+    kr1 = kr;
+    kr = pos_next<MESH>(g, kr);
   }
   __syncthreads();
   if (act && kend >= k0)
-    face_update(g, sc, tid, BX, NT, own.f, kend, k0, kend, i1, i2, i3, bdt, pwb, acc_prev, ob);
+    face_update<MESH>(g, sc, tid, BX, NT, own.f, kend, kr1, kr2, k0, kend, i1, i2, i3, bdt, pwb, acc_prev, ob);
   if (nbad && act) atomicAdd(sa.bad, 1);
   if (nfl && act) add_floor_count(sa.bad, (unsigned long long)nfl);
 }
@@ -748,7 +792,7 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
 // Uniform blocks: one workgroup per (tile, x3 segment, block), XCD-aware:
 // consecutive logical tiles land on the same XCD so that halo overlap hits its
 // L2.
-template <int RECON, int RS, class T, bool FL, bool MESH, bool MF, bool SAME = false, bool CHAR = false>
+template <int RECON, int RS, class T, bool FL, int MESH, bool MF, bool SAME = false, bool CHAR = false>
 __global__ void __launch_bounds__(T::NT) __attribute__((amdgpu_waves_per_eu(2)))
 k_stage_fused(UniformArgs a) {
   using S = Smem<RECON, T>;
@@ -768,14 +812,14 @@ k_stage_fused(UniformArgs a) {
                a.unb + blk * g.fblock, a.oc + blk * g.cblock, a.ob + blk * g.fblock,
                MF ? a.fm + blk * 3 * g.fvar : nullptr};
   const int k0 = g.ng + seg * a.kz;
-  const int kend = min(k0 + a.kz, g.ng + g.n3);
+  const int kend = min(k0 + a.kz, g.ng + (MESH == 2 ? g.mesh[2] * g.n3 : g.n3));
   stage_tile<RECON, RS, T, FL, MESH, MF, SAME, CHAR>(g, bp, a.sa, tile_x, tile_y, k0, kend, sp, sx, sc);
 }
 
 // Batched blocks of uneven sizes: a persistent grid whose workgroups pull
 // (block, tile, x3 segment) items from a device queue until it is drained.
-// MESH: the blocks tile one domain and read their exchanged ghost entries.
-template <int RECON, int RS, class T, bool FL, bool MF, bool SAME = false, bool MESH = false>
+// MESH 1: the blocks tile one domain and read their exchanged ghost entries.
+template <int RECON, int RS, class T, bool FL, bool MF, bool SAME = false, int MESH = 0>
 __global__ void __launch_bounds__(T::NT) __attribute__((amdgpu_waves_per_eu(2))) k_stage_batch(BatchArgs a) {
   using S = Smem<RECON, T>;
   __shared__ double sp[8 * S::PL];
@@ -804,10 +848,10 @@ __global__ void __launch_bounds__(T::NT) __attribute__((amdgpu_waves_per_eu(2)))
   }
 }
 
-// MESH: the blocks of a coupled mesh read their (exchanged) ghost entries; MF:
-// the face mass fluxes are stored for passive scalars.  Compile-time switches,
+// MESH: how neighbours are read; MF: the face mass fluxes are stored for
+// passive scalars.  Compile-time switches,
 // so that the plain periodic-block kernels keep their code.
-template <int RECON, int RS, class T, bool MESH, bool MF>
+template <int RECON, int RS, class T, int MESH, bool MF>
 hipError_t uniform_fl(const UniformArgs& fa, hipStream_t s) {
   const dim3 grid((unsigned)(8 * fa.per_xcd)), wg(T::NT);
   if constexpr (RECON == 0) {
@@ -825,7 +869,7 @@ hipError_t uniform_fl(const UniformArgs& fa, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int RECON, class T, bool MESH, bool MF>
+template <int RECON, class T, int MESH, bool MF>
 hipError_t uniform_rs(int rs, const UniformArgs& fa, hipStream_t s) {
   if (rs == 1) return uniform_fl<RECON, 1, T, MESH, MF>(fa, s);
   if (rs == 2) return uniform_fl<RECON, 2, T, MESH, MF>(fa, s);
@@ -835,8 +879,8 @@ hipError_t uniform_rs(int rs, const UniformArgs& fa, hipStream_t s) {
 template <int RS, class T>
 hipError_t charac_fl(const UniformArgs& fa, hipStream_t s) {
   const dim3 grid((unsigned)(8 * fa.per_xcd)), wg(T::NT);
-  if (fa.sa.fl.on()) hipLaunchKernelGGL((k_stage_fused<1, RS, T, true, false, false, false, true>), grid, wg, 0, s, fa);
-  else hipLaunchKernelGGL((k_stage_fused<1, RS, T, false, false, false, false, true>), grid, wg, 0, s, fa);
+  if (fa.sa.fl.on()) hipLaunchKernelGGL((k_stage_fused<1, RS, T, true, 0, false, false, true>), grid, wg, 0, s, fa);
+  else hipLaunchKernelGGL((k_stage_fused<1, RS, T, false, 0, false, false, true>), grid, wg, 0, s, fa);
   return hipGetLastError();
 }
 
@@ -852,7 +896,7 @@ hipError_t batch_fl(const BatchArgs& ba, int grid, hipStream_t s) {
 template <class T, int RECON, int RS, bool SAME>
 hipError_t batch_kind(const BatchArgs& ba, int grid, hipStream_t s, bool mesh) {
   if (mesh) {  // blocks that tile one domain (no floors, no mass fluxes)
-    hipLaunchKernelGGL((k_stage_batch<RECON, RS, T, false, false, SAME, true>), dim3(grid), dim3(T::NT), 0, s, ba);
+    hipLaunchKernelGGL((k_stage_batch<RECON, RS, T, false, false, SAME, 1>), dim3(grid), dim3(T::NT), 0, s, ba);
     return hipGetLastError();
   }
   return ba.fm ? batch_fl<T, RECON, RS, true, SAME>(ba, grid, s) : batch_fl<T, RECON, RS, false, SAME>(ba, grid, s);
@@ -862,9 +906,9 @@ hipError_t batch_kind(const BatchArgs& ba, int grid, hipStream_t s, bool mesh) {
 
 template <int RECON, class T>
 hipError_t launch_uniform(int rs, const UniformArgs& fa, hipStream_t s) {
-  if (fa.fm)
-    return fa.g.mesh[0] ? uniform_rs<RECON, T, true, true>(rs, fa, s) : uniform_rs<RECON, T, false, true>(rs, fa, s);
-  return fa.g.mesh[0] ? uniform_rs<RECON, T, true, false>(rs, fa, s) : uniform_rs<RECON, T, false, false>(rs, fa, s);
+  if (fa.fm) return fa.g.mesh[0] ? uniform_rs<RECON, T, 1, true>(rs, fa, s) : uniform_rs<RECON, T, 0, true>(rs, fa, s);
+  if (fa.domain) return uniform_rs<RECON, T, 2, false>(rs, fa, s);
+  return fa.g.mesh[0] ? uniform_rs<RECON, T, 1, false>(rs, fa, s) : uniform_rs<RECON, T, 0, false>(rs, fa, s);
 }
 
 template <class T>
