@@ -344,38 +344,39 @@ __device__ __forceinline__ int floor_values(double gm1, const Floors& fl, double
   return hit;
 }
 
-// The same reduction as a march along x3: one thread per (i, j) column of a
-// 64 x 4 tile of columns, over a segment of kz planes.  A cell's upper B3 is
-// the next cell's lower B3, kept in a register, so each face is read from
-// memory once: 64 B per cell against the grid-stride loop's re-reads of the
-// upper x2 and x3 faces.  The upper faces are found as cell_field finds them.
+// The same reduction as a march along x3: one thread per (i, j) column, 256
+// consecutive ones of a block (x1 fastest, so that no lane idles whatever the
+// block's width) per workgroup, over a segment of kz planes.  A cell's upper
+// B3 is the next cell's lower B3, kept in a register, so each face is read
+// from memory once: 64 B per cell against the grid-stride loop's re-reads of
+// the upper x2 and x3 faces.  Bound by HBM (5.1 TB/s at 256^3); on 64 x 4 tiles of
+// columns half the lanes idled on 32-wide blocks: 512 blocks of 32^3 288 -> 218
+// us.  The upper faces are found as cell_field finds them.
 // FLOOR: apply the floors of k_floor_state to each cell first, writing the
 // cells they change, so that the pass that ends a step with floors reads the
 // state once for both.
-constexpr int kMarchX = 64, kMarchY = kThreads / kMarchX;
 template <bool FLOOR>
-// Workgroups are numbered (tile, x3 segment, block), tile (x1 first) fastest;
+// Workgroups are numbered (columns, x3 segment, block), columns fastest;
 // launch slot s runs number (s mod 8) per_xcd + s / 8, so that neighbouring
 // tiles, which share cache lines at their x1 edges, run on one XCD and meet
 // in its L2.
 __global__ void __launch_bounds__(kThreads) k_newdt_march(Geo g, double gamma, Floors fl, double* __restrict__ cons,
-                                                         const double* __restrict__ bface, int ntx, int nty, int nseg,
-                                                         int kz, int total, int per_xcd,
+                                                         const double* __restrict__ bface, int ntiles, int nseg, int kz,
+                                                         int total, int per_xcd,
                                                          unsigned long long* __restrict__ dt_bits,
                                                          int* __restrict__ bad, CflEnd end) {
   const int logical = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
   if (logical >= total) return;  // the whole workgroup: the padding of the last XCD
-  const int ntiles = ntx * nty;
   const int tile = logical % ntiles, seg = (logical / ntiles) % nseg;
   const int b = logical / (ntiles * nseg);
-  const int i = g.ng + (tile % ntx) * kMarchX + (int)(threadIdx.x % kMarchX);
-  const int j = g.ng + (tile / ntx) * kMarchY + (int)(threadIdx.x / kMarchX);
+  const int col = tile * kThreads + (int)threadIdx.x;
+  const int i = g.ng + col % g.n1, j = g.ng + col / g.n1;
   const int k0 = g.ng + seg * kz, kend = min(k0 + kz, g.ng + g.n3);
   double* u = cons + (int64_t)b * g.cblock;
   const double* fb = bface + (int64_t)b * g.fblock;
   double best = DBL_MAX;
   int nbad = 0, nfloor = 0;
-  if (i < g.ng + g.n1 && j < g.ng + g.n2 && k0 < kend) {
+  if (j < g.ng + g.n2 && k0 < kend) {
     // this column's upper x1 and x2 faces: the stored ones (a composite's
     // blocks), the periodic image in the block, or the next block of a mesh
     const double* p1 = fb;
@@ -730,8 +731,8 @@ hipError_t launch_newdt(const Geo& g, double gamma, const double* cons, const do
                         bool floor) {
   // x3 segments: about 2 kDtBlocks workgroups in all (enough to fill the chip,
   // few enough atomics on the one result word), at least 8 planes each
-  const int ntx = (g.n1 + kMarchX - 1) / kMarchX, nty = (g.n2 + kMarchY - 1) / kMarchY;
-  const int64_t tiles = (int64_t)ntx * nty * std::max(nb, 1);
+  const int ntiles = (int)(((int64_t)g.n1 * g.n2 + kThreads - 1) / kThreads);
+  const int64_t tiles = (int64_t)ntiles * std::max(nb, 1);
   const int64_t want = (2 * kDtBlocks + tiles - 1) / tiles;
   const int nseg0 = (int)std::max<int64_t>(1, std::min<int64_t>(want, std::max(1, g.n3 / 8)));
   const int kz = (g.n3 + nseg0 - 1) / nseg0;
@@ -742,10 +743,10 @@ hipError_t launch_newdt(const Geo& g, double gamma, const double* cons, const do
   const dim3 grid((unsigned)(8 * per_xcd), 1u);
   if (floor)
     hipLaunchKernelGGL(k_newdt_march<true>, grid, dim3(kThreads), 0, s, g, gamma, fl, const_cast<double*>(cons), bface,
-                       ntx, nty, nseg, kz, (int)total, per_xcd, dt_bits, bad, end);
+                       ntiles, nseg, kz, (int)total, per_xcd, dt_bits, bad, end);
   else
     hipLaunchKernelGGL(k_newdt_march<false>, grid, dim3(kThreads), 0, s, g, gamma, fl, const_cast<double*>(cons),
-                       bface, ntx, nty, nseg, kz, (int)total, per_xcd, dt_bits, bad, end);
+                       bface, ntiles, nseg, kz, (int)total, per_xcd, dt_bits, bad, end);
   return hipGetLastError();
 }
 
