@@ -45,6 +45,7 @@ struct ScalarArgs {
   double* oc;            // stage output
   const double* fm;      // face mass fluxes, 3 face arrays per block
   int ntx, nty, nseg, kz;
+  int64_t total, per_xcd;  // workgroups doing work, ceil(total / 8)
 };
 
 struct ScalarBatchArgs {
@@ -56,6 +57,7 @@ struct ScalarBatchArgs {
   const double* unc;
   double* oc;
   const double* fm;  // laid out like bface
+  int total, per_xcd;
 };
 
 // Stored index of position idx along a direction with n active cells, for a
@@ -169,16 +171,24 @@ __device__ __forceinline__ void scalar_tile(const Geo& g, const ScalarCoef& sc, 
   }
 }
 
+// Bound by HBM: per cell the density and three mass fluxes, and per scalar its
+// mass, U^n's and the output.  Workgroups are numbered with the scalar fastest
+// and launch slot s runs number (s mod 8) per_xcd + s / 8, so that the scalars of
+// a tile run side by side on one XCD and the second reads density and fluxes
+// from its L2, as neighbouring tiles do their halos; one scalar after the other
+// over the whole block, each read them from memory (256^3 with 2 scalars,
+// PLM 493 -> 468 us, DC 391 -> 318 us).
 template <int RECON, bool FL, bool NEAR, bool MESH>
 __global__ void __launch_bounds__(kSX * kSY) k_scalar_stage(ScalarArgs a) {
   __shared__ double ring[ScalarRing<RECON, kSX, kSY>::R * ScalarRing<RECON, kSX, kSY>::PL];
   const Geo& g = a.g;
-  int64_t r = blockIdx.x;
+  int64_t r = (blockIdx.x % 8) * a.per_xcd + blockIdx.x / 8;
+  if (r >= a.total) return;  // the whole workgroup: the padding of the last XCD
+  const int v = (int)(r % g.ns); r /= g.ns;
   const int tile_x = (int)(r % a.ntx); r /= a.ntx;
   const int tile_y = (int)(r % a.nty); r /= a.nty;
-  const int seg = (int)(r % a.nseg); r /= a.nseg;
-  const int v = (int)(r % g.ns);
-  const int b = (int)(r / g.ns);
+  const int seg = (int)(r % a.nseg);
+  const int b = (int)(r / a.nseg);
   const int k0 = g.ng + seg * a.kz;
   const int kend = min(k0 + a.kz, g.ng + g.n3);
   scalar_tile<RECON, FL, NEAR, MESH, kSX, kSY>(g, a.sc, a.xc + b * g.cblock, a.unc + b * g.cblock,
@@ -190,8 +200,10 @@ __global__ void __launch_bounds__(kSX * kSY) k_scalar_stage(ScalarArgs a) {
 template <int RECON, bool FL, bool NEAR>
 __global__ void __launch_bounds__(kBT * kBT) k_scalar_batch(ScalarBatchArgs a) {
   __shared__ double ring[ScalarRing<RECON, kBT, kBT>::R * ScalarRing<RECON, kBT, kBT>::PL];
-  const WorkItem w = a.items[blockIdx.x / a.ns];
-  const int v = blockIdx.x % a.ns;
+  const int r = (int)((blockIdx.x % 8) * a.per_xcd + blockIdx.x / 8);  // numbered as in k_scalar_stage
+  if (r >= a.total) return;
+  const WorkItem w = a.items[r / a.ns];
+  const int v = r % a.ns;
   const BatchDesc& d = a.desc[w.block];
   scalar_tile<RECON, FL, NEAR, false, kBT, kBT>(d.g, a.sc, a.xc + d.coff, a.unc + d.coff, a.oc + d.coff,
                                                 a.fm + d.foff, a.fm, w.block, w.tile_x, w.tile_y, w.k0, w.kend, v,
@@ -231,7 +243,7 @@ hipError_t launch_scalar_stage(const Geo& g, int recon, const double* xc, const 
                                const double* fm, StageCoef coef, const double* dt_dev, double beta, int nb, Floors fl,
                                hipStream_t s) {
   if (g.ns <= 0) return hipSuccess;
-  ScalarArgs sa{g, ScalarCoef{coef, dt_dev, beta, fl}, xc, unc, outc, fm, 0, 0, 0, 0};
+  ScalarArgs sa{g, ScalarCoef{coef, dt_dev, beta, fl}, xc, unc, outc, fm, 0, 0, 0, 0, 0, 0};
   sa.ntx = (g.n1 + kSX - 1) / kSX;
   sa.nty = (g.n2 + kSY - 1) / kSY;
   // x3 segments: the longest of 32 .. 4 planes that still gives about 1024
@@ -242,14 +254,17 @@ hipError_t launch_scalar_stage(const Geo& g, int recon, const double* xc, const 
   sa.kz = kz < g.n3 ? kz : g.n3;
   sa.nseg = (g.n3 + sa.kz - 1) / sa.kz;
   const int64_t total = cols * sa.nseg;
-  if (total > 0x7fffffff) return hipErrorInvalidValue;
+  if (total > 0x7ffffff0) return hipErrorInvalidValue;
+  sa.total = total;
+  sa.per_xcd = (total + 7) / 8;
+  const unsigned grid = (unsigned)(8 * sa.per_xcd);
   // one correction step finds every periodic image a stencil reaches when each
   // direction has more active cells than the halo
   const int h = recon + 1;
   const bool near = g.n1 > h && g.n2 > h && g.n3 > h;
-  if (recon == 0) launch_f<0>(sa, near, (unsigned)total, s);
-  else if (recon == 1) launch_f<1>(sa, near, (unsigned)total, s);
-  else launch_f<2>(sa, near, (unsigned)total, s);
+  if (recon == 0) launch_f<0>(sa, near, grid, s);
+  else if (recon == 1) launch_f<1>(sa, near, grid, s);
+  else launch_f<2>(sa, near, grid, s);
   return hipGetLastError();
 }
 
@@ -260,11 +275,13 @@ hipError_t launch_scalar_stage_batch(const BatchDesc* desc, const WorkItem* item
                                      StageCoef coef, const double* dt_dev, double beta, Floors fl, hipStream_t s) {
   if (ns <= 0 || nitems <= 0) return hipSuccess;
   const int64_t total = (int64_t)nitems * ns;
-  if (total > 0x7fffffff) return hipErrorInvalidValue;
-  ScalarBatchArgs ba{desc, items, ns, ScalarCoef{coef, dt_dev, beta, fl}, xc, unc, outc, fm};
-  if (recon == 0) launch_bf<0>(ba, near, (unsigned)total, s);
-  else if (recon == 1) launch_bf<1>(ba, near, (unsigned)total, s);
-  else launch_bf<2>(ba, near, (unsigned)total, s);
+  if (total > 0x7ffffff0) return hipErrorInvalidValue;
+  ScalarBatchArgs ba{desc, items, ns, ScalarCoef{coef, dt_dev, beta, fl}, xc, unc, outc, fm, (int)total,
+                     (int)((total + 7) / 8)};
+  const unsigned grid = (unsigned)(8 * ba.per_xcd);
+  if (recon == 0) launch_bf<0>(ba, near, grid, s);
+  else if (recon == 1) launch_bf<1>(ba, near, grid, s);
+  else launch_bf<2>(ba, near, grid, s);
   return hipGetLastError();
 }
 
