@@ -48,6 +48,18 @@ class Config(C.Structure):
 
 
 _lib = None
+_tensor_lib = None
+_f64 = None
+
+
+def _torch():
+    """torch, imported by the first call that takes tensors"""
+    global _tensor_lib, _f64
+    if _tensor_lib is None:
+        import torch
+        _f64 = torch.float64
+        _tensor_lib = torch
+    return _tensor_lib
 
 
 def lib():
@@ -121,11 +133,22 @@ def _scalar_out(t, dtype: str):
     return C.c_void_p(t.data_ptr())
 
 
+_raw_stream = None  # current device's current stream as an address, set on first use
+
+
 def _stream(stream):
-    import torch
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream)
+    global _raw_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None:
+        import torch
+        get, dev = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+        if get is not None and dev is not None:
+            torch.cuda.init()
+            _raw_stream = lambda: get(dev())  # noqa: E731
+        else:
+            _raw_stream = lambda: torch.cuda.current_stream().cuda_stream  # noqa: E731
+    return _raw_stream()
 
 
 class Solver:
@@ -160,24 +183,39 @@ class Solver:
     def face_shape(self):
         return tuple(x + 1 for x in self.cell_shape)
 
-    def _arr(self, t, nvar, shape):
-        import torch
-        if not isinstance(t, torch.Tensor) or t.dtype != torch.float64 or not t.is_cuda:
+    def _arr(self, t, want):
+        """Address and block count of a tensor whose shape is want, or want
+        after a block axis."""
+        if not isinstance(t, _torch().Tensor) or t.dtype is not _f64 or not t.is_cuda:
             raise TypeError("expected a float64 tensor in HIP device memory")
         if not t.is_contiguous():
             raise ValueError("tensor must be contiguous")
-        sh = tuple(t.shape)
-        if sh == (nvar,) + shape:
+        sh = t.shape
+        if sh == want:
             nb = 1
-        elif len(sh) == 5 and sh[1:] == (nvar,) + shape:
+        elif len(sh) == 5 and sh[1:] == want:
             nb = sh[0]
         else:
-            raise ValueError(f"bad shape {sh}, expected (nb, {nvar}) + {shape}")
-        return C.c_void_p(t.data_ptr()), nb
+            raise ValueError(f"bad shape {tuple(sh)}, expected (nb,) + {want}")
+        return t.data_ptr(), nb
+
+    @property
+    def _cells(self):
+        w = self.__dict__.get("_cell_want")
+        if w is None:
+            w = self._cell_want = (self.nv,) + self.cell_shape
+        return w
+
+    @property
+    def _faces(self):
+        w = self.__dict__.get("_face_want")
+        if w is None:
+            w = self._face_want = (3,) + self.face_shape
+        return w
 
     def _pair(self, cons, bface):
-        pc, nb = self._arr(cons, self.nv, self.cell_shape)
-        pb, nb2 = self._arr(bface, 3, self.face_shape)
+        pc, nb = self._arr(cons, self._cells)
+        pb, nb2 = self._arr(bface, self._faces)
         if nb != nb2:
             raise ValueError("cons and bface hold different block counts")
         return pc, pb, nb
@@ -215,7 +253,7 @@ class Solver:
         pp, pb, nb = self._pair(prim, bface)
         if out is None:
             out = torch.empty_like(prim)
-        po, _ = self._arr(out, self.nv, self.cell_shape)
+        po, _ = self._arr(out, self._cells)
         _check(lib().athmhd_prim2cons(self._h, pp, pb, po, nb, _stream(stream)), self._h)
         return out
 
@@ -318,11 +356,11 @@ class Solver:
         part is added to g_bface in place.  Returns out_prim."""
         import torch
         pp, pb, nb = self._pair(prim, bface)
-        gc, _ = self._arr(g_cons, self.nv, self.cell_shape)
-        gbp, _ = self._arr(g_bface, 3, self.face_shape)
+        gc, _ = self._arr(g_cons, self._cells)
+        gbp, _ = self._arr(g_bface, self._faces)
         if out_prim is None:
             out_prim = torch.empty_like(prim)
-        op, _ = self._arr(out_prim, self.nv, self.cell_shape)
+        op, _ = self._arr(out_prim, self._cells)
         _check(lib().athmhd_prim2cons_vjp(self._h, pp, pb, gc, op, gbp, nb, _stream(stream)), self._h)
         return out_prim
 
