@@ -602,10 +602,10 @@ int alloc_adjoint(athmhd_t h) {
   if (h->adj_base) return ATHMHD_OK;
   const Geo& g = h->g;
   const int64_t state = g.cblock + g.fblock;
-  const int64_t nc = (int64_t)g.n1 * g.n2 * g.n3;
+  const int64_t cot = 8 * adj_slot_stride(g);
   const int nst = scheme_of(h->cfg.integrator).nstage;
   const int64_t nb = h->nbmax;
-  const int64_t total = ((nst - 1) * state + adj_scratch_per_block(g) + 3 * 8 * nc) * nb;
+  const int64_t total = ((nst - 1) * state + adj_scratch_per_block(g) + 3 * cot) * nb;
   if (hipMalloc(&h->adj_base, total * sizeof(double)) != hipSuccess) {
     (void)hipGetLastError();
     h->adj_base = nullptr;
@@ -620,7 +620,7 @@ int alloc_adjoint(athmhd_t h) {
   p += adj_scratch_per_block(g) * nb;
   for (int q = 0; q < 3; ++q) {
     h->adj_cot[q] = p;
-    p += 8 * nc * nb;
+    p += cot * nb;
   }
   return ATHMHD_OK;
 }

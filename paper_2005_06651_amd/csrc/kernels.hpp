@@ -211,8 +211,9 @@ hipError_t launch_floor_state_batch(const BatchDesc* desc, int nblocks, double g
 
 // ---- reverse mode (periodic uniform blocks) ---------------------------------
 // Cotangent sets are 8 active-only arrays per block (5 conserved variables,
-// then the lower face of each active cell for B1, B2, B3), x1 fastest, block
-// stride 8 * n1 * n2 * n3 doubles.
+// then the lower face of each active cell for B1, B2, B3), x1 fastest, array
+// stride adj_slot_stride doubles, block stride 8 times that.
+int64_t adj_slot_stride(const Geo& g);
 // Scratch doubles per block needed by launch_stage_vjp.
 int64_t adj_scratch_per_block(const Geo& g);
 // One stage of the reverse sweep for the spatial operator L of a stage

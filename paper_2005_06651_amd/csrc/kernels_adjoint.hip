@@ -30,6 +30,8 @@
 #include "kernels.hpp"
 #include "mhd_adjoint.hpp"
 
+#include <algorithm>
+
 namespace athmhd {
 
 namespace {
@@ -37,7 +39,7 @@ namespace {
 constexpr int kT = 256;
 inline unsigned grid_of(int64_t n) { return (unsigned)((n + kT - 1) / kT); }
 
-// Slots of the per-block scratch (each nc doubles, nc = active cells).
+// Slots of the per-block scratch (the active cells each, adj_slot_stride apart).
 enum : int {
   S_W = 0,     // 8: rho, v1, v2, v3, p, B1cc, B2cc, B3cc
   S_CE = 8,    // 3: cell EMF components
@@ -54,11 +56,23 @@ struct Adj {
   Geo g;          // padded layout of the caller's arrays
   int n[3];       // active cells per direction
   int st[3];      // strides of the active-only arrays: 1, n1, n1 n2
-  int64_t nc;     // active cells per block (< 2^31; 64-bit for slot offsets)
+  int64_t nc;     // active cells per block (< 2^31)
+  int64_t ss;     // doubles from one slot to the next (adj_slot_stride)
+  int chunk;      // consecutive workgroups that one XCD runs (cell_index)
   double idx[3];  // 1 / dx
   Gas gas;
   double ct_eps;
 };
+
+// Active cell of a thread.  Workgroups go round robin over the 8 XCDs, each
+// with its own L2: of every 8 chunk workgroups, chunk consecutive ones run on
+// one XCD, an eighth of a plane when that is chunk, so that the rows a thread
+// reads beside its own are mostly read by the same XCD (reverse kernels of a
+// 128^3 block 2 - 6 % faster than with chunk 1).  Threads past nc do nothing.
+__device__ __forceinline__ int cell_index(const Adj& a) {
+  const int b = blockIdx.x, C = a.chunk, r = b % (8 * C);
+  return (b - r + (r % 8) * C + r / 8) * kT + threadIdx.x;
+}
 
 __device__ __forceinline__ int wrapn(int t, int n) {
   while (t < 0) t += n;
@@ -108,20 +122,20 @@ __device__ __forceinline__ int pf(const Adj& a, const Cell& c, int d, int o) {
 __global__ void __launch_bounds__(kT) k_adj_prim(Adj a, const double* __restrict__ xc,
                                                 const double* __restrict__ xb, const double* __restrict__ V,
                                                 double* __restrict__ scr) {
-  const int t = blockIdx.x * kT + threadIdx.x;
+  const int t = cell_index(a);
   if (t >= (int)a.nc) return;
   const double* u = xc + blockIdx.y * a.g.cblock;
   const double* fb = xb + blockIdx.y * a.g.fblock;
-  double* s = scr + blockIdx.y * (S_TOTAL * a.nc);
+  double* s = scr + blockIdx.y * (S_TOTAL * a.ss);
   const Cell c = cell_of(a, t);
   {
-    const double* v = V + blockIdx.y * (8 * a.nc);
+    const double* v = V + blockIdx.y * (8 * a.ss);
 #pragma unroll
     for (int e = 0; e < 3; ++e) {
       const int ea = (e + 1) % 3, eb = (e + 2) % 3;
-      const double* va = v + (5 + ea) * a.nc;
-      const double* vb = v + (5 + eb) * a.nc;
-      s[(S_EB + e) * a.nc + t] =
+      const double* va = v + (5 + ea) * a.ss;
+      const double* vb = v + (5 + eb) * a.ss;
+      s[(S_EB + e) * a.ss + t] =
           (va[t] - va[at1(a, c, eb, -1)]) * a.idx[eb] - (vb[t] - vb[at1(a, c, ea, -1)]) * a.idx[ea];
     }
   }
@@ -133,17 +147,17 @@ __global__ void __launch_bounds__(kT) k_adj_prim(Adj a, const double* __restrict
   const double v[3] = {u[a.g.cvar + q] * ir, u[2 * a.g.cvar + q] * ir, u[3 * a.g.cvar + q] * ir};
   const double p = a.gas.gm1 * (u[4 * a.g.cvar + q] - 0.5 * rho * (v[0] * v[0] + v[1] * v[1] + v[2] * v[2]) -
                                 0.5 * (b[0] * b[0] + b[1] * b[1] + b[2] * b[2]));
-  s[(S_W + 0) * a.nc + t] = rho;
-  s[(S_W + 4) * a.nc + t] = p;
+  s[(S_W + 0) * a.ss + t] = rho;
+  s[(S_W + 4) * a.ss + t] = p;
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
-    s[(S_W + 1 + d) * a.nc + t] = v[d];
-    s[(S_W + 5 + d) * a.nc + t] = b[d];
+    s[(S_W + 1 + d) * a.ss + t] = v[d];
+    s[(S_W + 5 + d) * a.ss + t] = b[d];
   }
 #pragma unroll
   for (int e = 0; e < 3; ++e) {
     const int ea = (e + 1) % 3, eb = (e + 2) % 3;
-    s[(S_CE + e) * a.nc + t] = -(v[ea] * b[eb] - v[eb] * b[ea]);
+    s[(S_CE + e) * a.ss + t] = -(v[ea] * b[eb] - v[eb] * b[ea]);
   }
 }
 
@@ -182,7 +196,7 @@ __device__ __forceinline__ void face_states(const Adj& a, const double* __restri
                                             FaceState& L, FaceState& R) {
   double l[7], r[7];
 #pragma unroll
-  for (int m = 0; m < 7; ++m) recon_lr<RECON>(a, s + (S_W + wslot(D, m)) * a.nc, c, D, l[m], r[m]);
+  for (int m = 0; m < 7; ++m) recon_lr<RECON>(a, s + (S_W + wslot(D, m)) * a.ss, c, D, l[m], r[m]);
   L = FaceState{l[0], l[1], l[2], l[3], l[4], l[5], l[6]};
   R = FaceState{r[0], r[1], r[2], r[3], r[4], r[5], r[6]};
 }
@@ -190,10 +204,10 @@ __device__ __forceinline__ void face_states(const Adj& a, const double* __restri
 // ---- 2. face EMFs and upwind weights ---------------------------------------
 template <int D, int RECON, int RS>
 __global__ void __launch_bounds__(kT) k_adj_face_fwd(Adj a, const double* __restrict__ xb, double* __restrict__ scr) {
-  const int t = blockIdx.x * kT + threadIdx.x;
+  const int t = cell_index(a);
   if (t >= (int)a.nc) return;
   const double* fb = xb + blockIdx.y * a.g.fblock;
-  double* s = scr + blockIdx.y * (S_TOTAL * a.nc);
+  double* s = scr + blockIdx.y * (S_TOTAL * a.ss);
   const Cell c = cell_of(a, t);
   FaceState L, R;
   face_states<RECON>(a, s, c, D, L, R);
@@ -202,9 +216,9 @@ __global__ void __launch_bounds__(kT) k_adj_face_fwd(Adj a, const double* __rest
   double smax;
   if (RS == 1) hlld(L, R, bn, a.gas, F, smax);
   else hlle(L, R, bn, a.gas, F, smax);
-  s[(S_FE + 3 * D + 0) * a.nc + t] = F.bt2;   // EMF of component t1
-  s[(S_FE + 3 * D + 1) * a.nc + t] = -F.bt1;  // EMF of component t2
-  s[(S_FE + 3 * D + 2) * a.nc + t] = ct_weight(F.rho, 0.5 * (L.rho + R.rho), smax, a.ct_eps);
+  s[(S_FE + 3 * D + 0) * a.ss + t] = F.bt2;   // EMF of component t1
+  s[(S_FE + 3 * D + 1) * a.ss + t] = -F.bt1;  // EMF of component t2
+  s[(S_FE + 3 * D + 2) * a.ss + t] = ct_weight(F.rho, 0.5 * (L.rho + R.rho), smax, a.ct_eps);
 }
 
 // ---- 3. corner-EMF cotangents (computed in k_adj_prim) ---------------------
@@ -218,18 +232,18 @@ template <int D, int RECON, int RS>
 __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(2))) k_adj_face_bwd(Adj a, const double* __restrict__ xb,
                                                     const double* __restrict__ V, double* __restrict__ scr) {
   constexpr int T1 = (D + 1) % 3, T2 = (D + 2) % 3;
-  const int t = blockIdx.x * kT + threadIdx.x;
+  const int t = cell_index(a);
   if (t >= (int)a.nc) return;
   const double* fb = xb + blockIdx.y * a.g.fblock;
-  const double* v = V + blockIdx.y * (8 * a.nc);
-  double* s = scr + blockIdx.y * (S_TOTAL * a.nc);
+  const double* v = V + blockIdx.y * (8 * a.ss);
+  double* s = scr + blockIdx.y * (S_TOTAL * a.ss);
   const Cell c = cell_of(a, t);
-  const double* EB = s + S_EB * a.nc;
-  const double* CE = s + S_CE * a.nc;
-  const double* wT1 = s + (S_FE + 3 * T1 + 2) * a.nc;  // weights of the t1-faces
-  const double* wT2 = s + (S_FE + 3 * T2 + 2) * a.nc;  // weights of the t2-faces
-  const double* e5T1 = s + (S_FE + 3 * T1 + 0) * a.nc;  // t1-faces, EMF of their t1 component (= T2)
-  const double* e6T2 = s + (S_FE + 3 * T2 + 1) * a.nc;  // t2-faces, EMF of their t2 component (= T1)
+  const double* EB = s + S_EB * a.ss;
+  const double* CE = s + S_CE * a.ss;
+  const double* wT1 = s + (S_FE + 3 * T1 + 2) * a.ss;  // weights of the t1-faces
+  const double* wT2 = s + (S_FE + 3 * T2 + 2) * a.ss;  // weights of the t2-faces
+  const double* e5T1 = s + (S_FE + 3 * T1 + 0) * a.ss;  // t1-faces, EMF of their t1 component (= T2)
+  const double* e6T2 = s + (S_FE + 3 * T2 + 1) * a.ss;  // t2-faces, EMF of their t2 component (= T1)
   const int cm = at1(a, c, D, -1);
 
   // (a) EMF of component T2 carried by this face (edge component e = T2,
@@ -237,47 +251,47 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(2))) k_
   //     at c + T1.
   const int cp1 = at1(a, c, T1, 1);
   const int cp1m = at2(a, c, T1, 1, D, -1);
-  const double e6_b = EB[T2 * a.nc + t] * 0.25 * (3.0 - wT1[t] - wT1[cm]) +
-                      EB[T2 * a.nc + cp1] * 0.25 * (1.0 + wT1[cp1] + wT1[cp1m]);
+  const double e6_b = EB[T2 * a.ss + t] * 0.25 * (3.0 - wT1[t] - wT1[cm]) +
+                      EB[T2 * a.ss + cp1] * 0.25 * (1.0 + wT1[cp1] + wT1[cp1m]);
   // (b) EMF of component T1 (edge component T1, edge directions a = T2,
   //     b = D): eb0 of the edge at c, eb1 of the edge at c + T2.
   const int cp2 = at1(a, c, T2, 1);
   const int cp2m = at2(a, c, T2, 1, D, -1);
-  const double e5_b = EB[T1 * a.nc + t] * 0.25 * (3.0 - wT2[t] - wT2[cm]) +
-                      EB[T1 * a.nc + cp2] * 0.25 * (1.0 + wT2[cp2] + wT2[cp2m]);
+  const double e5_b = EB[T1 * a.ss + t] * 0.25 * (3.0 - wT2[t] - wT2[cm]) +
+                      EB[T1 * a.ss + cp2] * 0.25 * (1.0 + wT2[cp2] + wT2[cp2m]);
   // (c) upwind weight: wa0 / wa1 of the T2-edges at c and c + T1, wb0 / wb1
   //     of the T1-edges at c and c + T2.
   double w_b = 0.0;
   {
-    const double* ce = CE + T2 * a.nc;
+    const double* ce = CE + T2 * a.ss;
     // edge x = c: eb0 = e5T1[x], eb1 = e5T1[x - D]; c00, ca = x - D, cb = x - T1, cab
     {
       const double eb0 = e5T1[t], eb1 = e5T1[cm];
       const double c00 = ce[t], ca = ce[cm];
-      w_b += EB[T2 * a.nc + t] * (-0.25) * ((ca - eb1) - (c00 - eb0));
+      w_b += EB[T2 * a.ss + t] * (-0.25) * ((ca - eb1) - (c00 - eb0));
     }
     // edge x = c + T1 (this face is its wa1): eb0 = e5T1[x], eb1 = e5T1[x - D]
     {
       const double eb0 = e5T1[cp1], eb1 = e5T1[cp1m];
       const double cb = ce[t], cab = ce[cm];  // x - T1 = c, x - D - T1 = c - D
-      w_b += EB[T2 * a.nc + cp1] * 0.25 * ((eb1 - cab) - (eb0 - cb));
+      w_b += EB[T2 * a.ss + cp1] * 0.25 * ((eb1 - cab) - (eb0 - cb));
     }
   }
   {
-    const double* ce = CE + T1 * a.nc;
+    const double* ce = CE + T1 * a.ss;
     // edge x = c (this face is its wb0): ea0 = e6T2[x], ea1 = e6T2[x - D];
     // c00 = ce[x], ca = ce[x - T2], cb = ce[x - D]
     {
       const double ea0 = e6T2[t], ea1 = e6T2[cm];
       const double c00 = ce[t], cb = ce[cm];
-      w_b += EB[T1 * a.nc + t] * (-0.25) * ((cb - ea1) - (c00 - ea0));
+      w_b += EB[T1 * a.ss + t] * (-0.25) * ((cb - ea1) - (c00 - ea0));
     }
     // edge x = c + T2 (this face is its wb1): ca = ce[x - T2] = ce[c],
     // cab = ce[x - T2 - D] = ce[c - D]
     {
       const double ea0 = e6T2[cp2], ea1 = e6T2[cp2m];
       const double ca = ce[t], cab = ce[cm];
-      w_b += EB[T1 * a.nc + cp2] * 0.25 * ((ea1 - cab) - (ea0 - ca));
+      w_b += EB[T1 * a.ss + cp2] * 0.25 * ((ea1 - cab) - (ea0 - ca));
     }
   }
   // (d) flux cotangents: the face is the upper face of c - D and the lower
@@ -285,10 +299,10 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(2))) k_
   const double id = a.idx[D];
   FaceFlux Fb;
   Fb.rho = (v[t] - v[cm]) * id;
-  Fb.mn = (v[(1 + D) * a.nc + t] - v[(1 + D) * a.nc + cm]) * id;
-  Fb.mt1 = (v[(1 + T1) * a.nc + t] - v[(1 + T1) * a.nc + cm]) * id;
-  Fb.mt2 = (v[(1 + T2) * a.nc + t] - v[(1 + T2) * a.nc + cm]) * id;
-  Fb.e = (v[4 * a.nc + t] - v[4 * a.nc + cm]) * id;
+  Fb.mn = (v[(1 + D) * a.ss + t] - v[(1 + D) * a.ss + cm]) * id;
+  Fb.mt1 = (v[(1 + T1) * a.ss + t] - v[(1 + T1) * a.ss + cm]) * id;
+  Fb.mt2 = (v[(1 + T2) * a.ss + t] - v[(1 + T2) * a.ss + cm]) * id;
+  Fb.e = (v[4 * a.ss + t] - v[4 * a.ss + cm]) * id;
   Fb.bt1 = -e6_b;  // EMF of component T2 is -F.bt1
   Fb.bt2 = e5_b;   // EMF of component T1 is +F.bt2
   FaceState L, R;
@@ -302,51 +316,108 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(2))) k_
   const double rb[7] = {Rb.rho, Rb.vn, Rb.vt1, Rb.vt2, Rb.p, Rb.bt1, Rb.bt2};
 #pragma unroll
   for (int m = 0; m < 7; ++m) {
-    s[(S_LB + 7 * D + m) * a.nc + t] = lb[m];
-    s[(S_RB + 7 * D + m) * a.nc + t] = rb[m];
+    s[(S_LB + 7 * D + m) * a.ss + t] = lb[m];
+    s[(S_RB + 7 * D + m) * a.ss + t] = rb[m];
   }
-  s[(S_BN + D) * a.nc + t] = bn_b;
+  s[(S_BN + D) * a.ss + t] = bn_b;
 }
 
 // ---- 5. reverse of the reconstruction along D ------------------------------
 // Cell c feeds the right state of its lower face (c) and the left state of
 // its upper face (c + D); with PLM it also enters the slopes of c - D, c and
 // c + D.  Adds the contributions of direction D to the primitive cotangents.
-template <int D, int RECON>
-__device__ __forceinline__ void recon_bwd(const Adj& a, const double* __restrict__ s, const Cell& c, double* wb) {
-  const int t = c.t;
-  const int cp = at1(a, c, D, 1);
-  int cm = 0, cm2 = 0, cp2 = 0;
+
+// value of a scratch slot at a byte offset below 8 nc.  32 bits hold it: the
+// scratch of 2^29 cells would be 305 GB.  Slot base in scalar registers, one
+// 32-bit offset per neighbour for all slots.
+__device__ __forceinline__ double slot_at(const double* __restrict__ s, const Adj& a, int slot, unsigned o) {
+  return *(const double*)((const char*)(s + slot * a.ss) + o);
+}
+
+struct Nbr {
+  unsigned m2, m, p, p2;  // byte offsets of c - 2D, c - D, c + D, c + 2D
+};
+
+template <int RECON>
+__device__ __forceinline__ Nbr nbr_of(const Adj& a, const Cell& c, int d) {
+  Nbr n{0, 0, 8u * (unsigned)at1(a, c, d, 1), 0};
   if (RECON == 1) {
-    cm = at1(a, c, D, -1);
-    cm2 = at1(a, c, D, -2);
-    cp2 = at1(a, c, D, 2);
+    n.m2 = 8u * (unsigned)at1(a, c, d, -2);
+    n.m = 8u * (unsigned)at1(a, c, d, -1);
+    n.p2 = 8u * (unsigned)at1(a, c, d, 2);
   }
-#pragma unroll
-  for (int m = 0; m < 7; ++m) {
-    const double* lb = s + (S_LB + 7 * D + m) * a.nc;
-    const double* rb = s + (S_RB + 7 * D + m) * a.nc;
-    double g = rb[t] + lb[cp];
-    if (RECON == 1) {
-      const double* q = s + (S_W + wslot(D, m)) * a.nc;
-      // slope cotangents: delta(x) enters q_L(x + D) with +1/2, q_R(x) with -1/2
-      const double dbm = 0.5 * (lb[t] - rb[cm]);    // slope of c - D
-      const double db0 = 0.5 * (lb[cp] - rb[t]);    // slope of c
-      const double dbp = 0.5 * (lb[cp2] - rb[cp]);  // slope of c + D
-      const double qm2 = q[cm2], qm = q[cm], q0 = q[t], qp = q[cp], qp2 = q[cp2];
-      double x0 = 0.0, x1 = 0.0, x2 = 0.0;
-      vl_slope_vjp(qm2, qm, q0, dbm, x0, x1, x2);  // c is the right point
-      g += x2;
-      x0 = x1 = x2 = 0.0;
-      vl_slope_vjp(qm, q0, qp, db0, x0, x1, x2);  // c is the centre
-      g += x1;
-      x0 = x1 = x2 = 0.0;
-      vl_slope_vjp(q0, qp, qp2, dbp, x0, x1, x2);  // c is the left point
-      g += x0;
-    }
-    wb[wslot(D, m)] += g;
-    if (RECON == 1) __builtin_amdgcn_sched_barrier(0);  // one variable's loads at a time
+  return n;
+}
+
+// what one variable of one direction reads
+template <int RECON>
+struct ReconIn {
+  double r0, lp, l0, rm, l2, rp, qm2, qm, qp, qp2;
+};
+
+template <int D, int M, int RECON>
+__device__ __forceinline__ ReconIn<RECON> recon_in(const Adj& a, const double* __restrict__ s, unsigned o,
+                                                   const Nbr& n) {
+  ReconIn<RECON> v;
+  v.r0 = slot_at(s, a, S_RB + 7 * D + M, o);
+  v.lp = slot_at(s, a, S_LB + 7 * D + M, n.p);
+  if (RECON == 1) {
+    v.l0 = slot_at(s, a, S_LB + 7 * D + M, o);
+    v.rm = slot_at(s, a, S_RB + 7 * D + M, n.m);
+    v.l2 = slot_at(s, a, S_LB + 7 * D + M, n.p2);
+    v.rp = slot_at(s, a, S_RB + 7 * D + M, n.p);
+    v.qm2 = slot_at(s, a, S_W + wslot(D, M), n.m2);
+    v.qm = slot_at(s, a, S_W + wslot(D, M), n.m);
+    v.qp = slot_at(s, a, S_W + wslot(D, M), n.p);
+    v.qp2 = slot_at(s, a, S_W + wslot(D, M), n.p2);
   }
+  return v;
+}
+
+template <int RECON>
+__device__ __forceinline__ double recon_bwd(const ReconIn<RECON>& v, double q0) {
+  double g = v.r0 + v.lp;
+  if (RECON == 1) {
+    // slope cotangents: delta(x) enters q_L(x + D) with +1/2, q_R(x) with -1/2
+    const double dbm = 0.5 * (v.l0 - v.rm);  // slope of c - D
+    const double db0 = 0.5 * (v.lp - v.r0);  // slope of c
+    const double dbp = 0.5 * (v.l2 - v.rp);  // slope of c + D
+    const double d0 = v.qm - v.qm2, d1 = q0 - v.qm, d2 = v.qp - q0, d3 = v.qp2 - v.qp;
+    double lo, hi;
+    vl_slope_vjp(d0, d1, dbm, lo, hi);  // c is the right point
+    g += hi;
+    vl_slope_vjp(d1, d2, db0, lo, hi);  // c is the centre
+    g += lo - hi;
+    vl_slope_vjp(d2, d3, dbp, lo, hi);  // c is the left point
+    g -= lo;
+  }
+  return g;
+}
+
+// The 21 (direction, variable) pairs one after another; the loads of pair
+// I + 1 are issued before the arithmetic of pair I, which is scheduled as one
+// block: their latency is covered and no more than two pairs' are held.  Bound
+// by HBM: 66 slots read (a row's or plane's neighbours mostly from cache) and
+// 13 written.  One pair's loads after another's arithmetic, in 256 registers and 68 B
+// of scratch (2 waves per SIMD), took 652 us for a 128^3 block; this, in 112
+// registers (4 waves), 437, and 400 with the slots spread over the channels
+// (adj_slot_stride) and the rows of an XCD together (cell_index).
+template <int I, int RECON>
+__device__ __forceinline__ void recon_sweep(const Adj& a, const double* __restrict__ s, unsigned o, const Cell& c,
+                                            const Nbr& n, const ReconIn<RECON>& now, const double* w, double* wb) {
+  constexpr int D = I / 7, M = I % 7;
+  Nbr nn = n;
+  ReconIn<RECON> next;
+  if constexpr (I + 1 < 21) {
+    if constexpr (M == 6) nn = nbr_of<RECON>(a, c, D + 1);
+    next = recon_in<(I + 1) / 7, (I + 1) % 7, RECON>(a, s, o, nn);
+    if (RECON == 1) __builtin_amdgcn_sched_barrier(0);
+  }
+  wb[wslot(D, M)] += recon_bwd<RECON>(now, w[wslot(D, M)]);
+  // formed here: the compiler would sink the arithmetic to the stores and keep all that was loaded
+  asm volatile("" : "+v"(wb[wslot(D, M)]));
+  if (RECON == 1) __builtin_amdgcn_sched_barrier(0);
+  if constexpr (I + 1 < 21) recon_sweep<I + 1, RECON>(a, s, o, c, nn, next, w, wb);
 }
 
 // ---- 6. cell EMFs and cons -> prim in reverse -------------------------------
@@ -360,44 +431,41 @@ struct StageOut {
   int zfirst;
 };
 
-__device__ __forceinline__ void stage_out(const StageOut& so, int64_t off, int m, int64_t nc, int t, double jt) {
-  const int64_t e = off + m * nc + t;
+__device__ __forceinline__ void stage_out(const StageOut& so, int64_t off, int m, int64_t ss, int t, double jt) {
+  const int64_t e = off + m * ss + t;
   const double v = so.V[e];
   so.O[e] = so.g0 * v + so.scale * jt;
   if (so.Z) so.Z[e] = (so.zfirst ? 0.0 : so.Z[e]) + so.g1 * v;
 }
 
 template <int RECON>
-__global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(2))) k_adj_cell(Adj a,
+__global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(4))) k_adj_cell(Adj a,
                                                                                         double* __restrict__ scr,
                                                                                         StageOut so) {
-  const int t = blockIdx.x * kT + threadIdx.x;
+  const int t = cell_index(a);
   if (t >= (int)a.nc) return;
-  double* s = scr + blockIdx.y * (S_TOTAL * a.nc);
-  const int64_t off = blockIdx.y * (8 * a.nc);
+  double* s = scr + blockIdx.y * (S_TOTAL * a.ss);
+  const int64_t off = blockIdx.y * (8 * a.ss);
   const Cell c = cell_of(a, t);
   double wb[8], w[8];
 #pragma unroll
   for (int m = 0; m < 8; ++m) {
     wb[m] = 0.0;
-    w[m] = s[(S_W + m) * a.nc + t];
+    w[m] = s[(S_W + m) * a.ss + t];
   }
-  // one direction at a time: keeps the loads of the three directions from
-  // being hoisted together (register pressure)
-  recon_bwd<0, RECON>(a, s, c, wb);
-  __builtin_amdgcn_sched_barrier(0);
-  recon_bwd<1, RECON>(a, s, c, wb);
-  __builtin_amdgcn_sched_barrier(0);
-  recon_bwd<2, RECON>(a, s, c, wb);
-  __builtin_amdgcn_sched_barrier(0);
+  const unsigned o = 8u * (unsigned)t;
+  {
+    const Nbr n = nbr_of<RECON>(a, c, 0);
+    recon_sweep<0, RECON>(a, s, o, c, n, recon_in<0, 0, RECON>(a, s, o, n), w, wb);
+  }
   // cell EMF of component e enters the four corner EMFs of component e
   // around it (as c00, ca, cb, cab of the edges at c, c+a, c+b, c+a+b)
 #pragma unroll
   for (int e = 0; e < 3; ++e) {
     const int ea = (e + 1) % 3, eb = (e + 2) % 3;
-    const double* EB = s + (S_EB + e) * a.nc;
-    const double* wa = s + (S_FE + 3 * ea + 2) * a.nc;
-    const double* wbf = s + (S_FE + 3 * eb + 2) * a.nc;
+    const double* EB = s + (S_EB + e) * a.ss;
+    const double* wa = s + (S_FE + 3 * ea + 2) * a.ss;
+    const double* wbf = s + (S_FE + 3 * eb + 2) * a.ss;
     const int xa = at1(a, c, ea, 1), xb = at1(a, c, eb, 1), xab = at2(a, c, ea, 1, eb, 1);
     // weights of an edge x: wa0 = wa[x], wa1 = wa[x - b], wb0 = wbf[x], wb1 = wbf[x - a]
     const double g00 = -0.25 * ((1.0 - wa[t]) + (1.0 - wbf[t]));
@@ -419,26 +487,26 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(2))) k_
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
     urho -= wb[1 + d] * w[1 + d] * ir;
-    stage_out(so, off, 1 + d, a.nc, t, wb[1 + d] * ir - gm1 * w[1 + d] * pb);
-    s[(S_BC + d) * a.nc + t] = wb[5 + d] - gm1 * w[5 + d] * pb;
+    stage_out(so, off, 1 + d, a.ss, t, wb[1 + d] * ir - gm1 * w[1 + d] * pb);
+    s[(S_BC + d) * a.ss + t] = wb[5 + d] - gm1 * w[5 + d] * pb;
   }
-  stage_out(so, off, 0, a.nc, t, urho);
-  stage_out(so, off, 4, a.nc, t, gm1 * pb);
+  stage_out(so, off, 0, a.ss, t, urho);
+  stage_out(so, off, 4, a.ss, t, gm1 * pb);
 }
 
 // ---- 7. face-field cotangents -----------------------------------------------
 // B_d at the lower face of c: normal field of that face's Riemann problem and
 // half of the cell-centred field of c and of c - d.
 __global__ void __launch_bounds__(kT) k_adj_bface(Adj a, const double* __restrict__ scr, StageOut so) {
-  const int t = blockIdx.x * kT + threadIdx.x;
+  const int t = cell_index(a);
   if (t >= (int)a.nc) return;
-  const double* s = scr + blockIdx.y * (S_TOTAL * a.nc);
-  const int64_t off = blockIdx.y * (8 * a.nc);
+  const double* s = scr + blockIdx.y * (S_TOTAL * a.ss);
+  const int64_t off = blockIdx.y * (8 * a.ss);
   const Cell c = cell_of(a, t);
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
-    const double* bc = s + (S_BC + d) * a.nc;
-    stage_out(so, off, 5 + d, a.nc, t, s[(S_BN + d) * a.nc + t] + 0.5 * (bc[t] + bc[at1(a, c, d, -1)]));
+    const double* bc = s + (S_BC + d) * a.ss;
+    stage_out(so, off, 5 + d, a.ss, t, s[(S_BN + d) * a.ss + t] + 0.5 * (bc[t] + bc[at1(a, c, d, -1)]));
   }
 }
 
@@ -457,18 +525,18 @@ __global__ void __launch_bounds__(kT) k_adj_axpby(double* out, double x_coef, co
 // active entries of padded (cons, bface) -> 8 active-only arrays
 __global__ void __launch_bounds__(kT) k_adj_gather(Adj a, const double* __restrict__ gc,
                                                   const double* __restrict__ gb, double* __restrict__ V) {
-  const int t = blockIdx.x * kT + threadIdx.x;
+  const int t = cell_index(a);
   if (t >= (int)a.nc) return;
   const double* uc = gc + blockIdx.y * a.g.cblock;
   const double* ub = gb + blockIdx.y * a.g.fblock;
-  double* v = V + blockIdx.y * (8 * a.nc);
+  double* v = V + blockIdx.y * (8 * a.ss);
   const Cell c = cell_of(a, t);
   const int q = pc(a, c);
 #pragma unroll
-  for (int m = 0; m < 5; ++m) v[m * a.nc + t] = uc[m * a.g.cvar + q];
+  for (int m = 0; m < 5; ++m) v[m * a.ss + t] = uc[m * a.g.cvar + q];
   const int f = a.g.f(a.g.ng + c.x[0], a.g.ng + c.x[1], a.g.ng + c.x[2]);
 #pragma unroll
-  for (int d = 0; d < 3; ++d) v[(5 + d) * a.nc + t] = ub[d * a.g.fvar + f];
+  for (int d = 0; d < 3; ++d) v[(5 + d) * a.ss + t] = ub[d * a.g.fvar + f];
 }
 
 // padded outputs: active entries = X + Y (active-only arrays); every other
@@ -485,14 +553,14 @@ __global__ void __launch_bounds__(kT) k_adj_scatter_cons(Adj a, const double* __
   const int ng = a.g.ng;
   const bool act = i >= ng && i < ng + a.n[0] && j >= ng && j < ng + a.n[1] && k >= ng && k < ng + a.n[2];
   const int64_t at_ = act ? ((int64_t)(k - ng) * a.n[1] + (j - ng)) * a.n[0] + (i - ng) : 0;
-  const double* x = X + blockIdx.y * (8 * a.nc);
-  const double* y = Y + blockIdx.y * (8 * a.nc);
+  const double* x = X + blockIdx.y * (8 * a.ss);
+  const double* y = Y + blockIdx.y * (8 * a.ss);
   const double* gi = gin + blockIdx.y * a.g.cblock;
   double* go = gout + blockIdx.y * a.g.cblock;
 #pragma unroll
   for (int m = 0; m < 5; ++m) {
     const int64_t e = m * a.g.cvar + t;
-    go[e] = act ? x[m * a.nc + at_] + y[m * a.nc + at_] : gi[e];
+    go[e] = act ? x[m * a.ss + at_] + y[m * a.ss + at_] : gi[e];
   }
 }
 
@@ -507,14 +575,14 @@ __global__ void __launch_bounds__(kT) k_adj_scatter_bface(Adj a, const double* _
   const int ng = a.g.ng;
   const bool act = i >= ng && i < ng + a.n[0] && j >= ng && j < ng + a.n[1] && k >= ng && k < ng + a.n[2];
   const int64_t at_ = act ? ((int64_t)(k - ng) * a.n[1] + (j - ng)) * a.n[0] + (i - ng) : 0;
-  const double* x = X + blockIdx.y * (8 * a.nc);
-  const double* y = Y + blockIdx.y * (8 * a.nc);
+  const double* x = X + blockIdx.y * (8 * a.ss);
+  const double* y = Y + blockIdx.y * (8 * a.ss);
   const double* gi = gin + blockIdx.y * a.g.fblock;
   double* go = gout + blockIdx.y * a.g.fblock;
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
     const int64_t e = d * a.g.fvar + t;
-    go[e] = act ? x[(5 + d) * a.nc + at_] + y[(5 + d) * a.nc + at_] : gi[e];
+    go[e] = act ? x[(5 + d) * a.ss + at_] + y[(5 + d) * a.ss + at_] : gi[e];
   }
 }
 
@@ -583,6 +651,19 @@ __global__ void __launch_bounds__(kT) k_p2c_vjp_face(Geo g, const double* __rest
   }
 }
 
+}  // namespace
+
+// A thread reads the same cell of dozens of slots.  Slots of 2^21 doubles (a
+// 128^3 block) all map to one memory channel and one set of each cache; an odd
+// number of 256-byte lines between them spreads the slots of a cell.  Small
+// blocks, whose slots are few lines and which come in numbers, are not padded.
+int64_t adj_slot_stride(const Geo& g) {
+  const int64_t nc = (int64_t)g.n1 * g.n2 * g.n3;
+  return nc < 4096 ? nc : ((nc + 31) / 32 | 1) * 32;
+}
+
+namespace {
+
 Adj make_adj(const Geo& g, double gamma, double ct_eps) {
   Adj a;
   a.g = g;
@@ -590,6 +671,8 @@ Adj make_adj(const Geo& g, double gamma, double ct_eps) {
   a.n[1] = g.n2;
   a.n[2] = g.n3;
   a.nc = (int64_t)g.n1 * g.n2 * g.n3;
+  a.ss = adj_slot_stride(g);
+  a.chunk = std::max(1, std::min(32, g.n1 * g.n2 / (8 * kT)));
   a.st[0] = 1;
   a.st[1] = g.n1;
   a.st[2] = g.n1 * g.n2;
@@ -599,6 +682,12 @@ Adj make_adj(const Geo& g, double gamma, double ct_eps) {
   a.gas = Gas{gamma, gamma - 1.0, 1.0 / (gamma - 1.0)};
   a.ct_eps = ct_eps;
   return a;
+}
+
+// one thread per active cell, a whole number of the groups that cell_index permutes
+dim3 cell_grid(const Adj& a, int nb) {
+  const unsigned group = 8u * (unsigned)a.chunk;
+  return dim3((grid_of(a.nc) + group - 1) / group * group, (unsigned)nb);
 }
 
 template <int D, int RECON>
@@ -623,14 +712,14 @@ void face_dir(const Adj& a, int recon, int rs, dim3 grid, const double* xb, cons
 
 }  // namespace
 
-int64_t adj_scratch_per_block(const Geo& g) { return (int64_t)S_TOTAL * g.n1 * g.n2 * g.n3; }
+int64_t adj_scratch_per_block(const Geo& g) { return S_TOTAL * adj_slot_stride(g); }
 
 hipError_t launch_stage_vjp(const Geo& g, double gamma, int recon, int rs, double ct_eps, const double* xc,
                             const double* xb, const double* V, double* O, double g0, double scale, double* Z,
                             double g1, int zfirst, double* scr, int nb, hipStream_t s) {
   if (recon != 0 && recon != 1) return hipErrorInvalidValue;
   const Adj a = make_adj(g, gamma, ct_eps);
-  const dim3 grid(grid_of(a.nc), nb);
+  const dim3 grid = cell_grid(a, nb);
   hipLaunchKernelGGL(k_adj_prim, grid, dim3(kT), 0, s, a, xc, xb, V, scr);
   face_dir<0>(a, recon, rs, grid, xb, V, scr, s, false);
   face_dir<1>(a, recon, rs, grid, xb, V, scr, s, false);
@@ -660,7 +749,7 @@ hipError_t launch_adj_axpby(double* out, double xc, const double* x, double yc, 
 
 hipError_t launch_adj_gather(const Geo& g, const double* gc, const double* gb, double* V, int nb, hipStream_t s) {
   const Adj a = make_adj(g, 2.0, 0.0);
-  hipLaunchKernelGGL(k_adj_gather, dim3(grid_of(a.nc), nb), dim3(kT), 0, s, a, gc, gb, V);
+  hipLaunchKernelGGL(k_adj_gather, cell_grid(a, nb), dim3(kT), 0, s, a, gc, gb, V);
   return hipGetLastError();
 }
 

@@ -13,18 +13,16 @@
 namespace athmhd {
 
 // ---- van Leer slope: d = 2 dm dp / (dm + dp) if dm dp > 0, else 0 ----------
-// adjoint of d w.r.t. (qm, q0, qp)
-__device__ __forceinline__ void vl_slope_vjp(double qm, double q0, double qp, double d_b, double& qm_b, double& q0_b,
-                                             double& qp_b) {
-  const double dm = q0 - qm, dp = qp - q0;
-  if (!(dm * dp > 0.0)) return;
-  const double isum = frcp(dm + dp);
+// the cotangent d_b of d reaches dm = q0 - qm and dp = qp - q0.  Selects, not
+// branches: the kernel that calls it keeps the next variable's loads in flight
+// across it.
+__device__ __forceinline__ void vl_slope_vjp(double dm, double dp, double d_b, double& dm_b, double& dp_b) {
+  const bool on = dm * dp > 0.0;
+  const double isum = frcp(on ? dm + dp : 1.0);
   const double ddm = 2.0 * dp * dp * isum * isum;  // dd/ddm
   const double ddp = 2.0 * dm * dm * isum * isum;  // dd/ddp
-  const double dm_b = d_b * ddm, dp_b = d_b * ddp;
-  qm_b -= dm_b;
-  q0_b += dm_b - dp_b;
-  qp_b += dp_b;
+  dm_b = on ? d_b * ddm : 0.0;
+  dp_b = on ? d_b * ddp : 0.0;
 }
 
 // ---- fast magnetosonic speed (see fast_speed) -------------------------------
