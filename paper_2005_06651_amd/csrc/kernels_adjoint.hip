@@ -15,13 +15,14 @@
 //   1. k_adj_prim       primitives W and cell EMFs -v x B of the stage input
 //   2. k_adj_face_fwd   per direction: face EMFs and CT upwind weights
 //   3. (in k_adj_prim)  corner-EMF cotangents: transpose of the CT curl
-//   4. k_adj_face_bwd   per direction: flux / face-EMF / weight cotangents
-//                       gathered from the neighbouring cells and edges, then
-//                       the Riemann solver's reverse sweep -> cotangents of
-//                       the reconstructed states and of the normal field
-//   5-6. k_adj_cell     per cell: reverse of the reconstruction along each
-//                       direction into the primitive cotangents, the
-//                       cell-EMF cotangents and the reverse of cons -> prim
+//   4-5. k_adj_face_bwd per direction: flux / face-EMF / weight cotangents
+//                       gathered from the neighbouring cells and edges, the
+//                       Riemann solver's reverse sweep -> cotangents of the
+//                       reconstructed states and of the normal field, then
+//                       the reverse of the reconstruction -> cotangents of
+//                       the cells' primitives through that direction
+//   6. k_adj_cell       per cell: their sum, the cell-EMF cotangents and the
+//                       reverse of cons -> prim
 //   7. k_adj_bface      face-field cotangents (normal field of the Riemann
 //                       problems and the two cell-centred averages)
 // Steps 6 and 7 write the stage's output cotangent O = g0 V + scale J^T V and
@@ -45,11 +46,10 @@ enum : int {
   S_CE = 8,    // 3: cell EMF components
   S_FE = 11,   // 3 x 3: per face direction (EMF of component t1, of t2, weight)
   S_EB = 20,   // 3: corner-EMF cotangents
-  S_LB = 23,   // 3 x 7: cotangents of the left states of the faces, per direction
-  S_RB = 44,   // 3 x 7: of the right states
-  S_BN = 65,   // 3: cotangent of the normal field of the Riemann problems
-  S_BC = 68,   // 3: cotangent of the cell-centred field
-  S_TOTAL = 71
+  S_G = 23,    // 3 x 7: cotangents of a cell's primitives through the states of each direction
+  S_BN = 44,   // 3: cotangent of the normal field of the Riemann problems
+  S_BC = 47,   // 3: cotangent of the cell-centred field
+  S_TOTAL = 50
 };
 
 struct Adj {
@@ -227,17 +227,78 @@ __global__ void __launch_bounds__(kT) k_adj_face_fwd(Adj a, const double* __rest
 // (a = e+1, b = e+2 cyclic):
 //   Ebar_e = (v_Ba[c] - v_Ba[c - b]) / dx_b - (v_Bb[c] - v_Bb[c - a]) / dx_a
 
-// ---- 4. face cotangents and the Riemann solver's reverse sweep ------------
+// ---- 4. face cotangents, the Riemann solver and the reconstruction in reverse
+// Cell c feeds the right state of its lower face (c) and the left state of
+// its upper face (c + D); with PLM it also enters the slopes of c - D, c and
+// c + D.  One thread per face; the faces of a line along D follow one another
+// in a workgroup, so what a cell takes from its neighbours' faces and slopes
+// passes through LDS and only its 7 sums are stored: storing the 14 state
+// cotangents of each face and gathering them in k_adj_cell moved 56 more slots
+// per stage.
+//
+// The lines along D (kSpan cells of x1 side by side) are laid end to end, each
+// with the faces that its ends take from the periodic images (kLow before and
+// kHigh after); a workgroup takes kRows consecutive faces and completes the
+// cells with kLow of them before and kHigh after: whatever a line's length, no
+// face is idle but those.  Along x1 a wave is a workgroup, which waits for
+// nothing but itself; across x1 256 threads of 8 cells (PLM: 29 of 32 rows
+// complete a cell) or 16 (donor cell: 15 of 16) measured best of 8 and 16
+// cells on 128, 256 and 512 threads.
+//
+// Two waves per SIMD (256 registers): the sweep through the solver needs them,
+// so the slopes' differences wait for it in LDS (read again from memory they
+// cost 35 us of 280).  PLM on a 128^3 block: 189 us along x1, 243 along x2 and
+// x3, and 178 in k_adj_cell; the two-pass form took 206, 202, 192 and 400.
+// Donor cell 149, 173, 178 and 178; before 185, 187, 187 and 277.
+template <int D, int RECON>
+struct Line {
+  static constexpr int kSpan = D == 0 ? 1 : (RECON == 1 ? 8 : 16);
+  static constexpr int kB = D == 0 ? 64 : 256;  // threads
+  static constexpr int kRows = kB / kSpan;
+  static constexpr int kLow = RECON == 1 ? 1 : 0, kHigh = RECON == 1 ? 2 : 1;
+  static constexpr int kDone = kRows - kLow - kHigh;  // cells a workgroup completes
+};
+
+// number of workgroups
+template <int D, int RECON>
+int64_t line_groups(const Adj& a) {
+  typedef Line<D, RECON> L;
+  const int64_t lines =
+      D == 0 ? (int64_t)a.n[1] * a.n[2] : (int64_t)((a.n[0] + L::kSpan - 1) / L::kSpan) * a.n[3 - D];
+  return (lines * (a.n[D] + L::kLow + L::kHigh) + L::kDone - 1) / L::kDone;
+}
+
 template <int D, int RECON, int RS>
-__global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(2))) k_adj_face_bwd(Adj a, const double* __restrict__ xb,
-                                                    const double* __restrict__ V, double* __restrict__ scr) {
+__global__ void __launch_bounds__((Line<D, RECON>::kB)) __attribute__((amdgpu_waves_per_eu(2)))
+    k_adj_face_bwd(Adj a, int per_xcd, const double* __restrict__ xb, const double* __restrict__ V,
+                   double* __restrict__ scr) {
   constexpr int T1 = (D + 1) % 3, T2 = (D + 2) % 3;
-  const int t = cell_index(a);
-  if (t >= (int)a.nc) return;
+  typedef Line<D, RECON> L_;
+  constexpr int S = L_::kSpan, kB = L_::kB;
+  __shared__ double xl[7 * kB];  // left-state cotangents of the faces
+  __shared__ double xs[RECON == 1 ? 14 * kB : 1];  // a cell's lower and upper differences, then their cotangents
+  // (line, position) of this thread's face; consecutive workgroups, which share
+  // lines and planes, run on one XCD
+  const int wg = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
+  const int row = (int)threadIdx.x / S, span = a.n[D] + L_::kLow + L_::kHigh;
+  const int64_t seq = (int64_t)wg * L_::kDone + row;
+  const int line = (int)(seq / span), pos = (int)(seq % span) - L_::kLow;
+  const int groups = D == 0 ? 1 : (a.n[0] + S - 1) / S;  // of x1, per line of the two other directions
+  const int other = line / groups;
+  Cell c;
+  c.x[0] = D == 0 ? wrapn(pos, a.n[0]) : (line % groups) * S + (int)threadIdx.x % S;
+  c.x[1] = D == 1 ? wrapn(pos, a.n[1]) : (D == 0 ? other % a.n[1] : other);
+  c.x[2] = D == 2 ? wrapn(pos, a.n[2]) : (D == 0 ? other / a.n[1] : other);
+  const bool stored = c.x[0] < a.n[0] && c.x[1] < a.n[1] && c.x[2] < a.n[2];
+  // threads beyond the block repeat a cell of it
+  c.x[0] = min(c.x[0], a.n[0] - 1);
+  c.x[1] = min(c.x[1], a.n[1] - 1);
+  c.x[2] = min(c.x[2], a.n[2] - 1);
+  const bool mine = stored && pos >= 0 && pos < a.n[D] && row >= L_::kLow && row < L_::kLow + L_::kDone;
+  const int t = c.t = c.x[0] + c.x[1] * a.st[1] + c.x[2] * a.st[2];
   const double* fb = xb + blockIdx.y * a.g.fblock;
   const double* v = V + blockIdx.y * (8 * a.ss);
   double* s = scr + blockIdx.y * (S_TOTAL * a.ss);
-  const Cell c = cell_of(a, t);
   const double* EB = s + S_EB * a.ss;
   const double* CE = s + S_CE * a.ss;
   const double* wT1 = s + (S_FE + 3 * T1 + 2) * a.ss;  // weights of the t1-faces
@@ -306,7 +367,24 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(2))) k_
   Fb.bt1 = -e6_b;  // EMF of component T2 is -F.bt1
   Fb.bt2 = e5_b;   // EMF of component T1 is +F.bt2
   FaceState L, R;
-  face_states<RECON>(a, s, c, D, L, R);
+  const int tid = threadIdx.x;
+  if (RECON == 1) {
+    const int cm2 = at1(a, c, D, -2), cp = at1(a, c, D, 1);
+    double l[7], r[7];
+#pragma unroll
+    for (int m = 0; m < 7; ++m) {
+      const double* q = s + (S_W + wslot(D, m)) * a.ss;
+      const double qm = q[cm2], q0 = q[cm], q1 = q[t], q2 = q[cp];
+      l[m] = q0 + 0.5 * vl_slope(qm, q0, q1);
+      r[m] = q1 - 0.5 * vl_slope(q0, q1, q2);
+      xs[m * kB + tid] = q1 - q0;  // the differences of this cell's slope
+      xs[(7 + m) * kB + tid] = q2 - q1;
+    }
+    L = FaceState{l[0], l[1], l[2], l[3], l[4], l[5], l[6]};
+    R = FaceState{r[0], r[1], r[2], r[3], r[4], r[5], r[6]};
+  } else {
+    face_states<RECON>(a, s, c, D, L, R);
+  }
   const double bn = fb[D * a.g.fvar + pf(a, c, D, 0)];
   FaceState Lb{0, 0, 0, 0, 0, 0, 0}, Rb{0, 0, 0, 0, 0, 0, 0};
   double bn_b = 0.0;
@@ -314,110 +392,38 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(2))) k_
   else hlle_vjp(L, R, bn, a.gas, a.ct_eps, Fb, w_b, Lb, Rb, bn_b);
   const double lb[7] = {Lb.rho, Lb.vn, Lb.vt1, Lb.vt2, Lb.p, Lb.bt1, Lb.bt2};
   const double rb[7] = {Rb.rho, Rb.vn, Rb.vt1, Rb.vt2, Rb.p, Rb.bt1, Rb.bt2};
+  const int lo = max(tid - S, 0), hi = min(tid + S, kB - 1);
+#pragma unroll
+  for (int m = 0; m < 7; ++m) xl[m * kB + tid] = lb[m];
+  if (mine) s[(S_BN + D) * a.ss + t] = bn_b;
+  __syncthreads();
+  double g[7], own[7];
 #pragma unroll
   for (int m = 0; m < 7; ++m) {
-    s[(S_LB + 7 * D + m) * a.ss + t] = lb[m];
-    s[(S_RB + 7 * D + m) * a.ss + t] = rb[m];
+    const double lp = xl[m * kB + hi];
+    g[m] = rb[m] + lp;
+    if (RECON == 1) {
+      // slope cotangent: delta(c) enters q_L(c + D) with +1/2, q_R(c) with -1/2
+      double dm_b, dp_b;
+      vl_slope_vjp(xs[m * kB + tid], xs[(7 + m) * kB + tid], 0.5 * (lp - rb[m]), dm_b, dp_b);
+      xs[m * kB + tid] = dm_b;
+      xs[(7 + m) * kB + tid] = dp_b;
+      own[m] = dm_b - dp_b;
+    }
   }
-  s[(S_BN + D) * a.ss + t] = bn_b;
-}
-
-// ---- 5. reverse of the reconstruction along D ------------------------------
-// Cell c feeds the right state of its lower face (c) and the left state of
-// its upper face (c + D); with PLM it also enters the slopes of c - D, c and
-// c + D.  Adds the contributions of direction D to the primitive cotangents.
-
-// value of a scratch slot at a byte offset below 8 nc.  32 bits hold it: the
-// scratch of 2^29 cells would be 305 GB.  Slot base in scalar registers, one
-// 32-bit offset per neighbour for all slots.
-__device__ __forceinline__ double slot_at(const double* __restrict__ s, const Adj& a, int slot, unsigned o) {
-  return *(const double*)((const char*)(s + slot * a.ss) + o);
-}
-
-struct Nbr {
-  unsigned m2, m, p, p2;  // byte offsets of c - 2D, c - D, c + D, c + 2D
-};
-
-template <int RECON>
-__device__ __forceinline__ Nbr nbr_of(const Adj& a, const Cell& c, int d) {
-  Nbr n{0, 0, 8u * (unsigned)at1(a, c, d, 1), 0};
   if (RECON == 1) {
-    n.m2 = 8u * (unsigned)at1(a, c, d, -2);
-    n.m = 8u * (unsigned)at1(a, c, d, -1);
-    n.p2 = 8u * (unsigned)at1(a, c, d, 2);
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < 7; ++m) {
+      g[m] += xs[(7 + m) * kB + lo];  // c is the right point of the slope of c - D,
+      g[m] += own[m];                 // the centre of its own
+      g[m] -= xs[m * kB + hi];        // and the left point of that of c + D
+    }
   }
-  return n;
-}
-
-// what one variable of one direction reads
-template <int RECON>
-struct ReconIn {
-  double r0, lp, l0, rm, l2, rp, qm2, qm, qp, qp2;
-};
-
-template <int D, int M, int RECON>
-__device__ __forceinline__ ReconIn<RECON> recon_in(const Adj& a, const double* __restrict__ s, unsigned o,
-                                                   const Nbr& n) {
-  ReconIn<RECON> v;
-  v.r0 = slot_at(s, a, S_RB + 7 * D + M, o);
-  v.lp = slot_at(s, a, S_LB + 7 * D + M, n.p);
-  if (RECON == 1) {
-    v.l0 = slot_at(s, a, S_LB + 7 * D + M, o);
-    v.rm = slot_at(s, a, S_RB + 7 * D + M, n.m);
-    v.l2 = slot_at(s, a, S_LB + 7 * D + M, n.p2);
-    v.rp = slot_at(s, a, S_RB + 7 * D + M, n.p);
-    v.qm2 = slot_at(s, a, S_W + wslot(D, M), n.m2);
-    v.qm = slot_at(s, a, S_W + wslot(D, M), n.m);
-    v.qp = slot_at(s, a, S_W + wslot(D, M), n.p);
-    v.qp2 = slot_at(s, a, S_W + wslot(D, M), n.p2);
+  if (mine) {
+#pragma unroll
+    for (int m = 0; m < 7; ++m) s[(S_G + 7 * D + m) * a.ss + t] = g[m];
   }
-  return v;
-}
-
-template <int RECON>
-__device__ __forceinline__ double recon_bwd(const ReconIn<RECON>& v, double q0) {
-  double g = v.r0 + v.lp;
-  if (RECON == 1) {
-    // slope cotangents: delta(x) enters q_L(x + D) with +1/2, q_R(x) with -1/2
-    const double dbm = 0.5 * (v.l0 - v.rm);  // slope of c - D
-    const double db0 = 0.5 * (v.lp - v.r0);  // slope of c
-    const double dbp = 0.5 * (v.l2 - v.rp);  // slope of c + D
-    const double d0 = v.qm - v.qm2, d1 = q0 - v.qm, d2 = v.qp - q0, d3 = v.qp2 - v.qp;
-    double lo, hi;
-    vl_slope_vjp(d0, d1, dbm, lo, hi);  // c is the right point
-    g += hi;
-    vl_slope_vjp(d1, d2, db0, lo, hi);  // c is the centre
-    g += lo - hi;
-    vl_slope_vjp(d2, d3, dbp, lo, hi);  // c is the left point
-    g -= lo;
-  }
-  return g;
-}
-
-// The 21 (direction, variable) pairs one after another; the loads of pair
-// I + 1 are issued before the arithmetic of pair I, which is scheduled as one
-// block: their latency is covered and no more than two pairs' are held.  Bound
-// by HBM: 66 slots read (a row's or plane's neighbours mostly from cache) and
-// 13 written.  One pair's loads after another's arithmetic, in 256 registers and 68 B
-// of scratch (2 waves per SIMD), took 652 us for a 128^3 block; this, in 112
-// registers (4 waves), 437, and 400 with the slots spread over the channels
-// (adj_slot_stride) and the rows of an XCD together (cell_index).
-template <int I, int RECON>
-__device__ __forceinline__ void recon_sweep(const Adj& a, const double* __restrict__ s, unsigned o, const Cell& c,
-                                            const Nbr& n, const ReconIn<RECON>& now, const double* w, double* wb) {
-  constexpr int D = I / 7, M = I % 7;
-  Nbr nn = n;
-  ReconIn<RECON> next;
-  if constexpr (I + 1 < 21) {
-    if constexpr (M == 6) nn = nbr_of<RECON>(a, c, D + 1);
-    next = recon_in<(I + 1) / 7, (I + 1) % 7, RECON>(a, s, o, nn);
-    if (RECON == 1) __builtin_amdgcn_sched_barrier(0);
-  }
-  wb[wslot(D, M)] += recon_bwd<RECON>(now, w[wslot(D, M)]);
-  // formed here: the compiler would sink the arithmetic to the stores and keep all that was loaded
-  asm volatile("" : "+v"(wb[wslot(D, M)]));
-  if (RECON == 1) __builtin_amdgcn_sched_barrier(0);
-  if constexpr (I + 1 < 21) recon_sweep<I + 1, RECON>(a, s, o, c, nn, next, w, wb);
 }
 
 // ---- 6. cell EMFs and cons -> prim in reverse -------------------------------
@@ -438,10 +444,7 @@ __device__ __forceinline__ void stage_out(const StageOut& so, int64_t off, int m
   if (so.Z) so.Z[e] = (so.zfirst ? 0.0 : so.Z[e]) + so.g1 * v;
 }
 
-template <int RECON>
-__global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(4))) k_adj_cell(Adj a,
-                                                                                        double* __restrict__ scr,
-                                                                                        StageOut so) {
+__global__ void __launch_bounds__(kT) k_adj_cell(Adj a, double* __restrict__ scr, StageOut so) {
   const int t = cell_index(a);
   if (t >= (int)a.nc) return;
   double* s = scr + blockIdx.y * (S_TOTAL * a.ss);
@@ -453,11 +456,10 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(4))) k_
     wb[m] = 0.0;
     w[m] = s[(S_W + m) * a.ss + t];
   }
-  const unsigned o = 8u * (unsigned)t;
-  {
-    const Nbr n = nbr_of<RECON>(a, c, 0);
-    recon_sweep<0, RECON>(a, s, o, c, n, recon_in<0, 0, RECON>(a, s, o, n), w, wb);
-  }
+#pragma unroll
+  for (int d = 0; d < 3; ++d)
+#pragma unroll
+    for (int m = 0; m < 7; ++m) wb[wslot(d, m)] += s[(S_G + 7 * d + m) * a.ss + t];
   // cell EMF of component e enters the four corner EMFs of component e
   // around it (as c00, ca, cb, cab of the edges at c, c+a, c+b, c+a+b)
 #pragma unroll
@@ -697,8 +699,10 @@ void face_pair(const Adj& a, int rs, dim3 grid, const double* xb, const double* 
     if (rs == 1) hipLaunchKernelGGL((k_adj_face_fwd<D, RECON, 1>), grid, dim3(kT), 0, s, a, xb, scr);
     else hipLaunchKernelGGL((k_adj_face_fwd<D, RECON, 0>), grid, dim3(kT), 0, s, a, xb, scr);
   } else {
-    if (rs == 1) hipLaunchKernelGGL((k_adj_face_bwd<D, RECON, 1>), grid, dim3(kT), 0, s, a, xb, V, scr);
-    else hipLaunchKernelGGL((k_adj_face_bwd<D, RECON, 0>), grid, dim3(kT), 0, s, a, xb, V, scr);
+    const int per_xcd = (int)((line_groups<D, RECON>(a) + 7) / 8);
+    const dim3 lines(8u * (unsigned)per_xcd, grid.y);
+    if (rs == 1) hipLaunchKernelGGL((k_adj_face_bwd<D, RECON, 1>), lines, dim3(Line<D, RECON>::kB), 0, s, a, per_xcd, xb, V, scr);
+    else hipLaunchKernelGGL((k_adj_face_bwd<D, RECON, 0>), lines, dim3(Line<D, RECON>::kB), 0, s, a, per_xcd, xb, V, scr);
   }
 }
 
@@ -728,8 +732,7 @@ hipError_t launch_stage_vjp(const Geo& g, double gamma, int recon, int rs, doubl
   face_dir<1>(a, recon, rs, grid, xb, V, scr, s, true);
   face_dir<2>(a, recon, rs, grid, xb, V, scr, s, true);
   const StageOut so{V, O, Z, g0, g1, scale, zfirst};
-  if (recon == 0) hipLaunchKernelGGL((k_adj_cell<0>), grid, dim3(kT), 0, s, a, scr, so);
-  else hipLaunchKernelGGL((k_adj_cell<1>), grid, dim3(kT), 0, s, a, scr, so);
+  hipLaunchKernelGGL(k_adj_cell, grid, dim3(kT), 0, s, a, scr, so);
   hipLaunchKernelGGL(k_adj_bface, grid, dim3(kT), 0, s, a, scr, so);
   return hipGetLastError();
 }

@@ -14,8 +14,7 @@ namespace athmhd {
 
 // ---- van Leer slope: d = 2 dm dp / (dm + dp) if dm dp > 0, else 0 ----------
 // the cotangent d_b of d reaches dm = q0 - qm and dp = qp - q0.  Selects, not
-// branches: the kernel that calls it keeps the next variable's loads in flight
-// across it.
+// branches: the calls for the variables of a cell are scheduled together.
 __device__ __forceinline__ void vl_slope_vjp(double dm, double dp, double d_b, double& dm_b, double& dp_b) {
   const bool on = dm * dp > 0.0;
   const double isum = frcp(on ? dm + dp : 1.0);

@@ -1,7 +1,10 @@
 """Reverse mode at sizes where the layout of its scratch and the order of its
 workgroups change: from 4096 cells the arrays lie an odd number of 256-byte
 lines apart, and from 4096 cells in a plane each XCD runs several neighbouring
-workgroups (with a remainder group whose last threads have no cell).
+workgroups (with a remainder group whose last threads have no cell).  Lines of
+faces are laid end to end over workgroups that complete 61 or 63 cells of them
+along x1 and 29 or 15 (8 or 16 cells of x1 side by side) along x2 and x3: the
+last sizes put line ends and workgroup ends at and beside each other.
 
 Oracle: the transposition identity <w, J d> = <J^T w, d> with the CPU oracle's
 exact directional derivatives; both sides are sums of rounded products, whose
@@ -15,11 +18,12 @@ from test_gpu_adjoint import active_masks, athmhd, gpu_vjp, oracle_jvp, random_a
 
 pytestmark = pytest.mark.gpu
 
-SIZES = [(16, 16, 15), (16, 16, 16), (33, 17, 9), (64, 64, 3), (131, 65, 4)]
+SIZES = [(16, 16, 15), (16, 16, 16), (33, 17, 9), (64, 64, 3), (131, 65, 4),
+         (61, 9, 29), (63, 29, 12), (8, 30, 26), (17, 15, 61), (2, 3, 64), (1, 1, 5)]
 
 
 @pytest.mark.parametrize("n", SIZES)
-@pytest.mark.parametrize("integ,recon,rs", [("vl2", "plm", "hlld"), ("rk1", "plm", "hlle")])
+@pytest.mark.parametrize("integ,recon,rs", [("vl2", "plm", "hlld"), ("rk1", "plm", "hlle"), ("rk1", "dc", "hlld")])
 def test_transposition_over_layouts(torch_dev, athmhd, orc, n, integ, recon, rs):  # noqa: F811
     torch, dev = torch_dev
     blk = inputs.smooth_random(n=n, seed=23, ng=2)
