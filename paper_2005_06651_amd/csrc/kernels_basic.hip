@@ -351,7 +351,8 @@ __device__ __forceinline__ int floor_values(double gm1, const Floors& fl, double
 // from memory once: 64 B per cell against the grid-stride loop's re-reads of
 // the upper x2 and x3 faces.  Bound by HBM (5.1 TB/s at 256^3); on 64 x 4 tiles of
 // columns half the lanes idled on 32-wide blocks: 512 blocks of 32^3 288 -> 218
-// us.  The upper faces are found as cell_field finds them.
+// us.  The next plane is read while one is worked on (256^3 213 -> 205 us).  The
+// upper faces are found as cell_field finds them.
 // FLOOR: apply the floors of k_floor_state to each cell first, writing the
 // cells they change, so that the pass that ends a step with floors reads the
 // state once for both.
@@ -390,8 +391,12 @@ __global__ void __launch_bounds__(kThreads) k_newdt_march(Geo g, double gamma, F
       ju = g.ng;
       if (g.mesh[0]) p2 = bface + (int64_t)next_block<1>(g, b) * g.fblock;
     }
-    double b3lo = fb[2 * g.fvar + g.f(i, j, k0)];
-    for (int k = k0; k < kend; ++k) {
+    // one plane's values, read while the plane before it is worked on
+    struct Values {
+      double u[5], b1[2], b2[2], b3hi;
+    };
+    auto read = [&](int k) {
+      Values v;
       const double* p3 = fb;
       int ku = k + 1;
       if (g.mesh[0] >= 0 && ku == g.ng + g.n3) {
@@ -399,20 +404,32 @@ __global__ void __launch_bounds__(kThreads) k_newdt_march(Geo g, double gamma, F
         if (g.mesh[0]) p3 = bface + (int64_t)next_block<2>(g, b) * g.fblock;
       }
       const int q = g.c(i, j, k), f = g.f(i, j, k);
-      double uc[5] = {u[q], u[g.cvar + q], u[2 * g.cvar + q], u[3 * g.cvar + q], u[4 * g.cvar + q]};
-      const double b3hi = p3[2 * g.fvar + g.f(i, j, ku)];
-      const double bc[3] = {0.5 * (fb[f] + p1[g.f(iu, j, k)]), 0.5 * (fb[g.fvar + f] + p2[g.fvar + g.f(i, ju, k)]),
-                            0.5 * (b3lo + b3hi)};
+#pragma unroll
+      for (int m = 0; m < 5; ++m) v.u[m] = u[m * g.cvar + q];
+      v.b1[0] = fb[f];
+      v.b1[1] = p1[g.f(iu, j, k)];
+      v.b2[0] = fb[g.fvar + f];
+      v.b2[1] = p2[g.fvar + g.f(i, ju, k)];
+      v.b3hi = p3[2 * g.fvar + g.f(i, j, ku)];
+      return v;
+    };
+    double b3lo = fb[2 * g.fvar + g.f(i, j, k0)];
+    Values next = read(k0);
+    for (int k = k0; k < kend; ++k) {
+      Values v = next;
+      next = read(min(k + 1, kend - 1));
+      const double bc[3] = {0.5 * (v.b1[0] + v.b1[1]), 0.5 * (v.b2[0] + v.b2[1]), 0.5 * (b3lo + v.b3hi)};
       if (FLOOR) {
-        const int hit = floor_values(gamma - 1.0, fl, uc, bc);
-        if (hit & 1) u[q] = uc[0];
-        if (hit & 2) u[4 * g.cvar + q] = uc[4];
+        const int hit = floor_values(gamma - 1.0, fl, v.u, bc);
+        const int q = g.c(i, j, k);
+        if (hit & 1) u[q] = v.u[0];
+        if (hit & 2) u[4 * g.cvar + q] = v.u[4];
         nfloor += hit != 0;
       }
       double d;
-      if (cfl_cell(uc, bc, gamma, fl, g.dx1, g.dx2, g.dx3, d)) best = fmin(best, d);
+      if (cfl_cell(v.u, bc, gamma, fl, g.dx1, g.dx2, g.dx3, d)) best = fmin(best, d);
       else ++nbad;
-      b3lo = b3hi;
+      b3lo = v.b3hi;
     }
   }
   if (FLOOR && nfloor) add_floor_count(bad, (unsigned long long)nfloor);
@@ -752,11 +769,15 @@ hipError_t launch_newdt(const Geo& g, double gamma, const double* cons, const do
                         unsigned long long* dt_bits, const Floors& fl, int* bad, const CflEnd& end, hipStream_t s,
                         bool floor) {
   // x3 segments: about 2 kDtBlocks workgroups in all (enough to fill the chip,
-  // few enough atomics on the one result word), at least 8 planes each
+  // few enough atomics on the one result word), at least 8 planes each; down
+  // to 2 planes while there are no more than 256 workgroups, whose atomics (12
+  // ns each) cost less than the planes one after another: 64^3 11.9 us with 8
+  // planes, 9.2 with 4, 11.1 with 2; 64 x 32 x 32 11.5, 7.4 and 7.0
   const int ntiles = (int)(((int64_t)g.n1 * g.n2 + kThreads - 1) / kThreads);
   const int64_t tiles = (int64_t)ntiles * std::max(nb, 1);
   const int64_t want = (2 * kDtBlocks + tiles - 1) / tiles;
-  const int nseg0 = (int)std::max<int64_t>(1, std::min<int64_t>(want, std::max(1, g.n3 / 8)));
+  const int64_t most = std::max<int64_t>(g.n3 / 8, std::min<int64_t>(g.n3 / 2, 256 / tiles));
+  const int nseg0 = (int)std::max<int64_t>(1, std::min<int64_t>(want, most));
   const int kz = (g.n3 + nseg0 - 1) / nseg0;
   const int nseg = (g.n3 + kz - 1) / kz;
   const int64_t total = tiles * nseg;
