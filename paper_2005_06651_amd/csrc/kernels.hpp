@@ -125,6 +125,7 @@ inline bool mesh_domain(const Geo& g) {
 struct FusedPlan {
   bool small;  // 18 x 14 threads per workgroup instead of 34 x 15
   int kz;      // x3 planes per workgroup
+  bool lone;   // no two workgroups of 4 waves share a CU: one wave per SIMD
 };
 // the plan of a launch over nb blocks on a device of cus compute units;
 // kz_fixed > 0 prescribes the segment length

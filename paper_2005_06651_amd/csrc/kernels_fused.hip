@@ -14,14 +14,16 @@ namespace athmhd {
 //     tile (15.9 and 16.0 us per plane of a VL2 step), with PPM 0.95 of it, and
 //     0.9 when rounds follow each other, as their barriers then fall apart
 //     (RK3 at 256^3: 53.5 and 47.7 us per plane);
-//   * one workgroup alone on each CU takes 0.75 of a round (12 us);
+//   * one workgroup alone on each CU takes 0.75 of a round (12 us), with the PPM
+//     variant for it (lone) 0.6: 54 us x 0.57 per plane and round in RK3 at 48^3,
+//     56^3 and 64^3;
 //   * the last, partial round overlaps the one before it: at least half a
 //     round, else its share of the CUs (2.75 rounds at 128^3 measured 2.79,
 //     1.375 rounds 1.5).
-static double rounds_small(int64_t wgs, int cus, int recon) {
+static double rounds_small(int64_t wgs, int cus, int recon, bool lone) {
   const double r = (double)wgs / (2.0 * cus);
   const double full = std::floor(r), f = r - full;
-  const double tail = f == 0.0 ? 0.0 : full == 0.0 ? (f <= 0.5 ? 0.75 : 1.0) : std::max(0.5, f);
+  const double tail = f == 0.0 ? 0.0 : full == 0.0 ? (f <= 0.5 ? (lone ? 0.6 : 0.75) : 1.0) : std::max(0.5, f);
   return (full + tail) * (recon < 2 ? 1.0 : r < 4.0 ? 0.95 : 0.9);
 }
 
@@ -31,11 +33,12 @@ static double rounds_small(int64_t wgs, int cus, int recon) {
 // last round of workgroups nearly empty or the chip unfilled.  Measured with
 // the rule before (34 x 15 only, kz in 4, 8, .. 32 or 64) and now, per step:
 // 64^3 VL2+PLM 98 -> 83 us, 96^3 252 -> 193 us, 192^3 1415 -> 1242 us, 32^3 RK3+PPM
-// 363 -> 150 us, 200x150x131 RK3+PPM+HLLE 3.4 -> 2.6 ms; 256^3 VL2+PLM stays on
+// 363 -> 150 us (124 -> 104 sustained with the lone variant, 48^3 201 -> 165, 56^3
+// 280 -> 227, 64^3 298 -> 290), 200x150x131 RK3+PPM+HLLE 3.4 -> 2.6 ms; 256^3 VL2+PLM stays on
 // 34 x 15 and 32 planes (2.75 ms; 18 x 14: 2.94); RK3+PPM runs on 18 x 14 (9.1
 // and 8.9 ms).
 FusedPlan fused_plan(const Geo& geo, int recon, int nb, int cus, int kz_fixed) {
-  FusedPlan best{false, 1};
+  FusedPlan best{false, 1, false};
   Geo g = geo;
   if (mesh_domain(geo)) {
     g.n1 *= geo.mesh[0];
@@ -50,14 +53,17 @@ FusedPlan fused_plan(const Geo& geo, int recon, int nb, int cus, int kz_fixed) {
   for (int kz = lo; kz <= hi; ++kz) {
     const int nseg = (g.n3 + kz - 1) / kz;
     const double planes = std::min(kz, g.n3) + 2.5;
-    const double u = planes * (double)((cols_u * nseg + cus - 1) / cus), v = planes * rounds_small(cols_s * nseg, cus, recon);
+    // the variant for a CU of one's own: PPM of periodic blocks without scalars
+    const bool lone = recon == 2 && cols_s * nseg <= cus && geo.mesh[0] == 0 && geo.ns == 0;
+    const double u = planes * (double)((cols_u * nseg + cus - 1) / cus);
+    const double v = planes * rounds_small(cols_s * nseg, cus, recon, lone);
     if (u < cost) {
       cost = u;
-      best = FusedPlan{false, kz};
+      best = FusedPlan{false, kz, false};
     }
     if (v < cost) {
       cost = v;
-      best = FusedPlan{true, kz};
+      best = FusedPlan{true, kz, lone};
     }
   }
   return best;
@@ -95,6 +101,7 @@ hipError_t launch_stage_fused(const Geo& g, double gamma, int recon, int rs, dou
   fa.fm = fm;
   fa.kz = plan.kz;
   fa.domain = mesh_domain(g);
+  fa.lone = plan.lone;
   const int n1 = fa.domain ? g.mesh[0] * g.n1 : g.n1, n2 = fa.domain ? g.mesh[1] * g.n2 : g.n2;
   const int n3 = fa.domain ? g.mesh[2] * g.n3 : g.n3;
   const int TX = plan.small ? TileS::TX : TileU::TX, TY = plan.small ? TileS::TY : TileU::TY;

@@ -494,10 +494,45 @@ __device__ __forceinline__ void ppm_cell(double qa, double qb, double qc, double
   }
 }
 
+// The same two steps with selects for branches: every operation is done, but
+// nothing waits for a branch and the seven variables of a cell are scheduled
+// together.  For a wave that is alone on its SIMD (see k_stage_fused); where
+// another wave fills the waits it is slower (256^3: 0.79x).
+__device__ __forceinline__ double ppm_face_flat(double qm1, double q0, double q1, double q2) {
+  const double qf = (7.0 / 12.0) * (q0 + q1) - (1.0 / 12.0) * (qm1 + q2);
+  const double d2 = 3.0 * (q0 - 2.0 * qf + q1);
+  const double d2l = qm1 - 2.0 * q0 + q1;
+  const double d2r = q0 - 2.0 * q1 + q2;
+  const double ql = 0.5 * (q0 + q1) - cs_lim3(d2, d2l, d2r) * (1.0 / 6.0);
+  return (qf - q0) * (q1 - qf) < 0.0 ? ql : qf;
+}
+
+__device__ __forceinline__ void ppm_cell_flat(double qa, double qb, double qc, double qd, double qe, double& qm,
+                                              double& qp) {
+  constexpr double C = 1.25;
+  const bool extremum = (qp - qc) * (qc - qm) <= 0.0 || (qb - qc) * (qc - qd) <= 0.0;
+  const double d2 = 6.0 * (qm + qp) - 12.0 * qc;
+  const double d2c = qb - 2.0 * qc + qd;
+  const double d2l = qa - 2.0 * qb + qc;
+  const double d2r = qc - 2.0 * qd + qe;
+  double num = fmin(fabs(d2), C * fmin(fabs(d2c), fmin(fabs(d2l), fabs(d2r)))), den = fabs(d2);
+  const bool same = same_sign(d2, d2c, d2l, d2r);
+  const int e = den < 0x1p-900 ? 900 : 0;
+  num = ldexp(num, e);
+  den = ldexp(den, e);
+  const double r = same && den != 0.0 ? num * frcp(den) : 0.0;
+  const double dqm = qm - qc, dqp = qp - qc;
+  const double mp = fabs(dqp) >= 2.0 * fabs(dqm) ? qc - 2.0 * dqm : qp;
+  const double mm = fabs(dqm) >= 2.0 * fabs(mp - qc) ? qc - 2.0 * (mp - qc) : qm;
+  const double em = qc + dqm * r, ep = qc + dqp * r;
+  qm = extremum ? em : mm;
+  qp = extremum ? ep : mp;
+}
+
 // Reconstruct the two edge values of cell c from a line of cells centred on
 // it (Sec. 3.2.1): s[LA + o] = q_{c+o}, o in [-LA, LA], with LA = 0, 1, 2 for
-// DC, PLM, PPM; returns (left edge, right edge).
-template <int RECON>
+// DC, PLM, PPM; returns (left edge, right edge).  FLAT: PPM without branches.
+template <int RECON, bool FLAT = false>
 __device__ __forceinline__ void cell_edges(const double* s, double& left, double& right) {
   if (RECON == 0) {
     left = s[0];
@@ -507,9 +542,10 @@ __device__ __forceinline__ void cell_edges(const double* s, double& left, double
     left = s[1] - 0.5 * d;
     right = s[1] + 0.5 * d;
   } else {
-    double qm = ppm_face(s[0], s[1], s[2], s[3]);
-    double qp = ppm_face(s[1], s[2], s[3], s[4]);
-    ppm_cell(s[0], s[1], s[2], s[3], s[4], qm, qp);
+    double qm = FLAT ? ppm_face_flat(s[0], s[1], s[2], s[3]) : ppm_face(s[0], s[1], s[2], s[3]);
+    double qp = FLAT ? ppm_face_flat(s[1], s[2], s[3], s[4]) : ppm_face(s[1], s[2], s[3], s[4]);
+    if (FLAT) ppm_cell_flat(s[0], s[1], s[2], s[3], s[4], qm, qp);
+    else ppm_cell(s[0], s[1], s[2], s[3], s[4], qm, qp);
     left = qm;
     right = qp;
   }

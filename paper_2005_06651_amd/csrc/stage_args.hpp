@@ -45,6 +45,7 @@ struct UniformArgs {
   double* ob;
   double* fm;  // NULL, or the face mass-flux output of every block (3 face arrays per block)
   bool domain;  // the tiles cover the domain of a coupled mesh (mesh_domain), not its blocks
+  bool lone;    // every workgroup has a CU to itself (FusedPlan)
   int ntx, nty, nseg, kz;
   int64_t total;    // workgroups doing work
   int64_t per_xcd;  // ceil(total / 8)

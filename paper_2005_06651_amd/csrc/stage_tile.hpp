@@ -303,7 +303,7 @@ __device__ __forceinline__ void face_update(const Geo& g, const double* __restri
 // plane (row: the cell, st: stride of the direction), in the face's frame (map;
 // nrm: slot of the cell-centred normal field).
 // own_edges: left and right edge of the own cell.
-template <int RECON>
+template <int RECON, bool FLAT>
 __device__ __forceinline__ void own_edges(const double* __restrict__ sp, int PL, int row, int st, const int (&map)[7],
                                           double* lo, double* hi) {
   constexpr int NW = 2 * RECON + 1;
@@ -312,7 +312,12 @@ __device__ __forceinline__ void own_edges(const double* __restrict__ sp, int PL,
     double line[NW];
 #pragma unroll
     for (int o = 0; o < NW; ++o) line[o] = sp[map[v] * PL + row + (o - RECON) * st];
-    cell_edges<RECON>(line, lo[v], hi[v]);
+    cell_edges<RECON, FLAT>(line, lo[v], hi[v]);
+    if (FLAT) {
+      // one variable at a time: all masks of 14 limiters at once spill scalar registers
+      asm volatile("" : "+v"(lo[v]), "+v"(hi[v]));
+      __builtin_amdgcn_sched_barrier(0);
+    }
   }
 }
 
@@ -362,7 +367,8 @@ __device__ __forceinline__ void face_states(const double* __restrict__ sp, int P
 // with its neighbour through LDS, which is full), 58 registers spilled; the
 // five-kernel pipeline with 7 x 7 eliminations it replaces took 5.97 ms per
 // VL2+HLLD step at 192^3, of which the donor-cell predictor 1.6 ms; now 1.97 ms.
-template <int RECON, int RS, class T, bool FL, int MESH = 0, bool MF = false, bool SAME = false, bool CHAR = false>
+template <int RECON, int RS, class T, bool FL, int MESH = 0, bool MF = false, bool SAME = false, bool CHAR = false,
+          bool LONE = false>
 __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, const StageArgs& sa, int tile_x,
                                            int tile_y, int k0, int kend, double* __restrict__ sp,
                                            double* __restrict__ sx, double* __restrict__ sc) {
@@ -548,7 +554,7 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
 #pragma unroll
         for (int o = 0; o < NW; ++o) line[o] = win[o].q[v];
         double left, right;
-        cell_edges<RECON>(line, left, right);
+        cell_edges<RECON, LONE>(line, left, right);
         zl[v] = qz_carry[v];
         zr[v] = left;
         qz_carry[v] = right;
@@ -615,10 +621,10 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
     double xr[7], yr[7];  // right states of the own faces
     if constexpr (EDGES) {
       double hi[7];
-      own_edges<RECON>(sp, PL, row, 1, mapx, xr, hi);
+      own_edges<RECON, LONE>(sp, PL, row, 1, mapx, xr, hi);
 #pragma unroll
       for (int v = 0; v < 7; ++v) sx[slotx[v] * NT + tid] = hi[v];
-      own_edges<RECON>(sp, PL, row, PW, mapy, yr, hi);
+      own_edges<RECON, LONE>(sp, PL, row, PW, mapy, yr, hi);
 #pragma unroll
       for (int v = 0; v < 7; ++v) sx[sloty[v] * NT + tid] = hi[v];
       __syncthreads();
@@ -792,8 +798,12 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
 // Uniform blocks: one workgroup per (tile, x3 segment, block), XCD-aware:
 // consecutive logical tiles land on the same XCD so that halo overlap hits its
 // L2.
-template <int RECON, int RS, class T, bool FL, int MESH, bool MF, bool SAME = false, bool CHAR = false>
-__global__ void __launch_bounds__(T::NT) __attribute__((amdgpu_waves_per_eu(2)))
+// LONE (PPM on the 4-wave tile, launches with no more workgroups than CUs): a
+// wave has its SIMD to itself, 512 registers and nobody to fill its waits, so
+// PPM's limiters run without branches.  64x32x32 stage 56 -> 48 us; with two waves
+// per SIMD the branches win (256^3: 0.79x without).
+template <int RECON, int RS, class T, bool FL, int MESH, bool MF, bool SAME = false, bool CHAR = false, bool LONE = false>
+__global__ void __launch_bounds__(T::NT) __attribute__((amdgpu_waves_per_eu(LONE ? 1 : 2)))
 k_stage_fused(UniformArgs a) {
   using S = Smem<RECON, T>;
   __shared__ double sp[8 * S::PL];      // primitives of the current plane
@@ -813,7 +823,7 @@ k_stage_fused(UniformArgs a) {
                MF ? a.fm + blk * 3 * g.fvar : nullptr};
   const int k0 = g.ng + seg * a.kz;
   const int kend = min(k0 + a.kz, g.ng + (MESH == 2 ? g.mesh[2] * g.n3 : g.n3));
-  stage_tile<RECON, RS, T, FL, MESH, MF, SAME, CHAR>(g, bp, a.sa, tile_x, tile_y, k0, kend, sp, sx, sc);
+  stage_tile<RECON, RS, T, FL, MESH, MF, SAME, CHAR, LONE>(g, bp, a.sa, tile_x, tile_y, k0, kend, sp, sx, sc);
 }
 
 // Batched blocks of uneven sizes: a persistent grid whose workgroups pull
@@ -861,6 +871,15 @@ hipError_t uniform_fl(const UniformArgs& fa, hipStream_t s) {
         hipLaunchKernelGGL((k_stage_fused<RECON, RS, T, true, MESH, MF, true>), grid, wg, 0, s, fa);
       else
         hipLaunchKernelGGL((k_stage_fused<RECON, RS, T, false, MESH, MF, true>), grid, wg, 0, s, fa);
+      return hipGetLastError();
+    }
+  }
+  if constexpr (RECON == 2 && T::NT <= 256 && MESH == 0 && !MF) {
+    if (fa.lone) {
+      if (fa.sa.fl.on())
+        hipLaunchKernelGGL((k_stage_fused<RECON, RS, T, true, 0, false, false, false, true>), grid, wg, 0, s, fa);
+      else
+        hipLaunchKernelGGL((k_stage_fused<RECON, RS, T, false, 0, false, false, false, true>), grid, wg, 0, s, fa);
       return hipGetLastError();
     }
   }
