@@ -2,7 +2,7 @@
 //
 // Each workgroup (34 x 15 threads, 8 wave64s, or one of the smaller tiles of
 // stage_args.hpp) owns a tile of 32 x 13 active columns in (x1, x2) plus a
-// one-cell ring, and marches along x3 over a segment of KZ planes.  Per plane
+// one-cell ring, and marches along x3 over a segment of kz planes.  Per plane
 // everything stays on chip:
 //   * every thread owns one column of the region; it converts its column's
 //     conserved state to primitives (Sec. 3.1) one plane ahead of use and keeps
@@ -433,7 +433,7 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
   constexpr bool RELOAD_BN = LA >= 2;
   constexpr int NBQ = RELOAD_BN ? 1 : LA + 1;
   double bnq[NBQ][3];
-  // next own plane to load, and planes p, p - 1 and p - 2
+  // next own plane to load, and planes p, p - 1 and p - 2 (the last two: not with MESH 0)
   Pos ka = pos_at<MESH>(g, k0 - 1 - LA), kr = pos_at<MESH>(g, k0 - 1), kr1 = kr, kr2 = kr;
   {
     double w[8];
@@ -478,6 +478,10 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
 
   for (int p = k0 - 1; p <= kend; ++p) {
     const bool zface = p >= k0;
+    // the segment's planes p, p - 1, p - 2: plain indices for periodic blocks (the
+    // cursors kept for them cost the batch 48 bytes of spill, 4 %), the cursors
+    // elsewhere (coupled batch 4.50 ms with them, 4.60 without)
+    const Pos w0 = MESH ? kr : Pos{p, 0}, w1 = MESH ? kr1 : Pos{p - 1, 0}, w2 = MESH ? kr2 : Pos{p - 2, 0};
     // ---- 1-2. shift the window and convert the look-ahead plane p+LA
 #pragma unroll
     for (int o = 0; o < NW - 1; ++o) win[o] = win[o + 1];
@@ -568,7 +572,7 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
         fz_cons[0] = fz.rho; fz_cons[1] = fz.mt1; fz_cons[2] = fz.mt2; fz_cons[3] = fz.mn; fz_cons[4] = fz.e;
         e2z = -fz.bt1;
         e1z = fz.bt2;
-        if (MF && act && p < kend) put(face_plane<MESH>(g, bp.fm, 2, kr), own.f, fz.rho);
+        if (MF && act && p < kend) put(face_plane<MESH>(g, bp.fm, 2, w0), own.f, fz.rho);
       }
     }
     if (ring) {
@@ -596,7 +600,7 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
     // ---- 8, for plane p-1: its face-field updates from the corner EMFs that
     // the previous iteration left in sc
     if (act && p - 1 >= k0)
-      face_update<MESH>(g, sc, tid, BX, NT, own.f, p - 1, kr1, kr2, k0, kend, i1, i2, i3, bdt, pwb, acc_prev, ob);
+      face_update<MESH>(g, sc, tid, BX, NT, own.f, p - 1, w1, w2, k0, kend, i1, i2, i3, bdt, pwb, acc_prev, ob);
 
     if (PF == 0) {
       ka = pos_next<MESH>(g, ka);
@@ -640,7 +644,7 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
         face_states<RECON, CHAR>(sp, PL, row, 1, mapx, 5, sa.gas.gamma, ql, xr);
       }
       riemann<RS, FL>(ql, xr, bnq[0][0], sa.gas, sa.ct_eps, sa.fl, nfl, fx, wx);
-      if (MF && act && p >= k0 && p < kend) put(face_plane<MESH>(g, bp.fm, 0, kr), own.f, fx.rho);
+      if (MF && act && p >= k0 && p < kend) put(face_plane<MESH>(g, bp.fm, 0, w0), own.f, fx.rho);
       // x1-face E3 = -F(B2), E2 = +F(B3)
       e3x = -fx.bt1;
       e2x = fx.bt2;
@@ -668,7 +672,7 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
       if constexpr (!EDGES) face_states<RECON, CHAR>(sp, PL, row, PW, mapy, 6, sa.gas.gamma, yl, yr);
       FaceFlux fy;
       riemann<RS, FL>(yl, yr, bnq[0][1], sa.gas, sa.ct_eps, sa.fl, nfl, fy, wy);
-      if (MF && act && p >= k0 && p < kend) put(face_plane<MESH>(g, bp.fm, 1, kr), own.f, fy.rho);
+      if (MF && act && p >= k0 && p < kend) put(face_plane<MESH>(g, bp.fm, 1, w0), own.f, fy.rho);
       sx[(X_FY + 0) * NT + tid] = fy.rho;
       sx[(X_FY + 1) * NT + tid] = fy.mt2;  // M1
       sx[(X_FY + 2) * NT + tid] = fy.mn;   // M2
@@ -691,8 +695,9 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
     const bool out_cell = act && zface && p - 1 >= k0;
     double un[8], xg[8];
     if constexpr (!SAME) {
-      const Pos first = pos_at<MESH>(g, k0);
-      const Pos qc = p > k0 ? kr1 : first, qf = p < k0 ? first : (p < kend ? kr : kr1);
+      const Pos first = MESH ? pos_at<MESH>(g, k0) : Pos{k0, 0};
+      const Pos qc = MESH == 0 ? Pos{max(p - 1, k0), 0} : p > k0 ? kr1 : first;
+      const Pos qf = MESH == 0 ? Pos{min(max(p, k0), kend - 1), 0} : p < k0 ? first : (p < kend ? kr : kr1);
       const Col c = here(own);
 #pragma unroll
       for (int v = 0; v < 5; ++v) un[v] = at(cell_plane<MESH>(g, unc, v, qc), c.c);
@@ -758,7 +763,7 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
       }
       if (out_cell) {
 #pragma unroll
-        for (int v = 0; v < 5; ++v) put(cell_plane<MESH>(g, oc, v, kr1), own.c, pw[v] + bdt * acc_prev[v]);
+        for (int v = 0; v < 5; ++v) put(cell_plane<MESH>(g, oc, v, w1), own.c, pw[v] + bdt * acc_prev[v]);
       }
 #pragma unroll
       for (int v = 0; v < 5; ++v) acc_prev[v] = acc[v];
@@ -790,7 +795,8 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
   }
   __syncthreads();
   if (act && kend >= k0)
-    face_update<MESH>(g, sc, tid, BX, NT, own.f, kend, kr1, kr2, k0, kend, i1, i2, i3, bdt, pwb, acc_prev, ob);
+    face_update<MESH>(g, sc, tid, BX, NT, own.f, kend, MESH ? kr1 : Pos{kend, 0},
+                      MESH ? kr2 : Pos{kend - 1, 0}, k0, kend, i1, i2, i3, bdt, pwb, acc_prev, ob);
   if (nbad && act) atomicAdd(sa.bad, 1);
   if (nfl && act) add_floor_count(sa.bad, (unsigned long long)nfl);
 }
