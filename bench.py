@@ -38,25 +38,25 @@ ALG_FLOPS_PER_ZONE_CYCLE = 2560.0
 # on this workload, scaled by the counters of a plain 1 GiB copy, and the hash
 # of the stage-kernel sources they were measured on (traffic is reported only
 # while the sources are unchanged).
-STAGE_TRAFFIC = {"bytes_per_launch": 2.977e+09, "fetch_bytes_per_launch": 1.858e+09,
-                 "write_bytes_per_launch": 1.120e+09, "fetch_scale": 1.9999, "write_scale": 1.0000,
-                 "source_hash": "d9dccd87daa965a6"}
+STAGE_TRAFFIC = {"bytes_per_launch": 3.178e+09, "fetch_bytes_per_launch": 2.053e+09,
+                 "write_bytes_per_launch": 1.126e+09, "fetch_scale": 1.9999, "write_scale": 1.0000,
+                 "source_hash": "c4bdb23c9b897b0c"}
 # FP64 VALU issue of the same stage launches (rocprofv3 SQ_INSTS_VALU per
 # launch over 256 CUs x 2.4 GHz x the launch duration, mean of the DC and PLM
 # stages) and the stage time those launches took under the profiler: with the
 # traffic above they say which roof binds (the larger measured fraction).
-STAGE_ISSUE = {"valu_issue_frac": 0.508, "profiled_ms_per_launch": 1.6894, "source_hash": "d9dccd87daa965a6"}
+STAGE_ISSUE = {"valu_issue_frac": 0.529, "profiled_ms_per_launch": 1.5873, "source_hash": "c4bdb23c9b897b0c"}
 HBM_FRAC_TARGET = 0.60       # the HBM-roofline fraction the stage kernel is measured against
 # The same for the level operators on the 256^3 block (per octant launch).
 LEVELS_SOURCES = ("kernels_amr.hip", "common.hpp")
-LEVELS_TRAFFIC = {"prolong": {"bytes_per_launch": 1.635e+09, "fetch_bytes_per_launch": 3.96e+08,
-                              "write_bytes_per_launch": 1.24e+09},
-                  "restrict": {"bytes_per_launch": 1.112e+09, "fetch_bytes_per_launch": 9.696e+08,
-                               "write_bytes_per_launch": 1.423e+08},
+LEVELS_TRAFFIC = {"prolong": {"bytes_per_launch": 1.436e+09, "fetch_bytes_per_launch": 2.077e+08,
+                              "write_bytes_per_launch": 1.229e+09},
+                  "restrict": {"bytes_per_launch": 1.098e+09, "fetch_bytes_per_launch": 9.592e+08,
+                               "write_bytes_per_launch": 1.386e+08},
                   "prolong_primitive": {"bytes_per_launch": 1.799e+09,
-                                        "fetch_bytes_per_launch": 5.624e+08,
-                                        "write_bytes_per_launch": 1.236e+09},
-                  "fetch_scale": 1.9999, "write_scale": 1.0000, "source_hash": "52cd612e9ccca04c"}
+                                        "fetch_bytes_per_launch": 5.618e+08,
+                                        "write_bytes_per_launch": 1.237e+09},
+                  "fetch_scale": 1.9999, "write_scale": 1.0000, "source_hash": "62484bd5f1eafa87"}
 
 
 def parse():
