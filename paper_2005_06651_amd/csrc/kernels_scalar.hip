@@ -108,22 +108,42 @@ __device__ __forceinline__ void scalar_tile(const Geo& g, const ScalarCoef& sc, 
   const double bdt = sc.dt_dev ? sc.beta * *sc.dt_dev : sc.cf.bdt;
   const double i1 = 1.0 / g.dx1, i2 = 1.0 / g.dx2, i3 = 1.0 / g.dx3;
 
-  // C of plane z (with its halo) into ring slot `slot`
-  auto load_plane = [&](int z, int slot) {
-    const int kk = read_sc<MESH, NEAR>(z, g.n3, g.ng);
-    for (int e = tid; e < PL; e += NT) {
-      const int ii = read_sc<MESH, NEAR>(x0 - H + e % PW, g.n1, g.ng);
-      const int jj = read_sc<MESH, NEAR>(y0 - H + e / PW, g.n2, g.ng);
-      const int q = g.c(ii, jj, kk);
-      double rho = xb[q];
+  // This thread's cells of a plane with its halo: their offsets in a plane, and
+  // what C = (rho C) / rho needs of them, read one plane ahead of its use: the
+  // loads, like those of the mass fluxes below, are on their way while the
+  // plane before is worked on.
+  constexpr int NE = (PL + NT - 1) / NT;
+  int col[NE];
+#pragma unroll
+  for (int n = 0; n < NE; ++n) {
+    const int e = min(tid + n * NT, PL - 1);
+    col[n] = g.c(read_sc<MESH, NEAR>(x0 - H + e % PW, g.n1, g.ng), read_sc<MESH, NEAR>(y0 - H + e / PW, g.n2, g.ng), 0);
+  }
+  double rho[NE], mass[NE], en[NE];
+  auto fetch = [&](int z) {
+    const int at = g.c(0, 0, read_sc<MESH, NEAR>(z, g.n3, g.ng));
+#pragma unroll
+    for (int n = 0; n < NE; ++n) {
+      rho[n] = xb[at + col[n]];
+      mass[n] = sv[at + col[n]];
+      if (FL) en[n] = xb[4 * g.cvar + at + col[n]];
+    }
+  };
+  auto store = [&](int slot) {
+#pragma unroll
+    for (int n = 0; n < NE; ++n) {
       // with floors, C uses the density of the floored primitives
-      if (FL && isfinite(rho) && isfinite(xb[4 * g.cvar + q]) && !(rho >= sc.fl.d)) rho = sc.fl.d;
-      ring[slot * PL + e] = sv[q] / rho;
+      if (FL && isfinite(rho[n]) && isfinite(en[n]) && !(rho[n] >= sc.fl.d)) rho[n] = sc.fl.d;
+      if (tid + n * NT < PL) ring[slot * PL + tid + n * NT] = mass[n] / rho[n];
     }
   };
 
 #pragma unroll
-  for (int z = 0; z < 2 * H; ++z) load_plane(k0 - H + z, z);
+  for (int z = 0; z < 2 * H; ++z) {
+    fetch(k0 - H + z);
+    store(z);
+  }
+  fetch(k0 + H);
   // upper faces: the block's own lower faces, or on the upper boundary the
   // lower boundary face of the next block (the block itself when periodic)
   const int ip = wrap_sc<NEAR>(i + 1, g.n1, g.ng), jp = wrap_sc<NEAR>(j + 1, g.n2, g.ng);
@@ -134,7 +154,19 @@ __device__ __forceinline__ void scalar_tile(const Geo& g, const ScalarCoef& sc, 
   double f3lo = act ? fm[2 * g.fvar + g.f(i, j, k0)] : 0.0;
   for (int p = k0; p < kend; ++p) {
     const int base = p - k0;  // ring index of plane p - H
-    load_plane(p + H, (base + 2 * H) % R);
+    double f1lo = 0.0, f1up = 0.0, f2lo = 0.0, f2up = 0.0, f3up = 0.0, un = 0.0, x = 0.0;
+    const int64_t e = (5 + v) * g.cvar + g.c(i, j, p);
+    if (act) {
+      f1lo = fm[g.f(i, j, p)];
+      f1up = fm1[g.f(ip, j, p)];
+      f2lo = fm[g.fvar + g.f(i, j, p)];
+      f2up = fm2[g.fvar + g.f(i, jp, p)];
+      f3up = (p + 1 == g.ng + g.n3 ? fm3 : fm)[2 * g.fvar + g.f(i, j, wrap_sc<NEAR>(p + 1, g.n3, g.ng))];
+      un = unb[e];
+      if (sc.cf.g0 != 0.0) x = xb[e];
+    }
+    store((base + 2 * H) % R);
+    if (p + 1 < kend) fetch(p + 1 + H);
     __syncthreads();
     if (act) {
       double lx[NW], ly[NW], lz[NW];
@@ -145,9 +177,6 @@ __device__ __forceinline__ void scalar_tile(const Geo& g, const ScalarCoef& sc, 
         ly[o] = pc[l + (o - H) * PW];
         lz[o] = ring[((base + o) % R) * PL + l];
       }
-      const double f1lo = fm[g.f(i, j, p)], f1up = fm1[g.f(ip, j, p)];
-      const double f2lo = fm[g.fvar + g.f(i, j, p)], f2up = fm2[g.fvar + g.f(i, jp, p)];
-      const double f3up = (p + 1 == g.ng + g.n3 ? fm3 : fm)[2 * g.fvar + g.f(i, j, wrap_sc<NEAR>(p + 1, g.n3, g.ng))];
       const double* lines[3] = {lx, ly, lz};
       const double flo[3] = {f1lo, f2lo, f3lo}, fup[3] = {f1up, f2up, f3up}, inv[3] = {i1, i2, i3};
       double sum = 0.0;
@@ -162,9 +191,8 @@ __device__ __forceinline__ void scalar_tile(const Geo& g, const ScalarCoef& sc, 
         const double flux_up = fup[d] >= 0.0 ? fup[d] * r0 : fup[d] * lp;
         sum += (flux_up - flux_lo) * inv[d];
       }
-      const int64_t e = (5 + v) * g.cvar + g.c(i, j, p);
-      double out = sc.cf.g1 * unb[e];
-      if (sc.cf.g0 != 0.0) out += sc.cf.g0 * xb[e];
+      double out = sc.cf.g1 * un;
+      if (sc.cf.g0 != 0.0) out += sc.cf.g0 * x;
       ob[e] = out - bdt * sum;
       f3lo = f3up;
     }
@@ -177,7 +205,9 @@ __device__ __forceinline__ void scalar_tile(const Geo& g, const ScalarCoef& sc, 
 // a tile run side by side on one XCD and the second reads density and fluxes
 // from its L2, as neighbouring tiles do their halos; one scalar after the other
 // over the whole block, each read them from memory (256^3 with 2 scalars,
-// PLM 493 -> 468 us, DC 391 -> 318 us).
+// PLM 493 -> 468 us, DC 391 -> 318 us).  Reading a plane ahead, and the fluxes before
+// the plane's conversion, brought PLM from 503 to 459 us in another run (DC 324 and
+// 326); held to 64 registers for 8 waves per SIMD it spills: 500.
 template <int RECON, bool FL, bool NEAR, bool MESH>
 __global__ void __launch_bounds__(kSX * kSY) k_scalar_stage(ScalarArgs a) {
   __shared__ double ring[ScalarRing<RECON, kSX, kSY>::R * ScalarRing<RECON, kSX, kSY>::PL];
