@@ -1364,8 +1364,12 @@ int athmhd_newdt(athmhd_t h, const double* cons, const double* bface, int nblock
   if (rc) return rc;
   if (!dt_host) return fail(h, ATHMHD_EINVAL, "NULL dt_host");
   hipStream_t s = (hipStream_t)stream;
-  // the reduction leaves dt and the count in the handle's pinned host words
+  // the reduction leaves dt and the count in the handle's pinned host words;
+  // no reduction leaves a NaN, so that one which did not end is not taken for
+  // the call before it
   char* hp = (char*)h->h_pinned;
+  const double none = std::nan("");
+  std::memcpy(hp, &none, 8);
   CflEnd end;
   end.dt = (double*)hp;
   end.nbad = (int32_t*)(hp + 8);
@@ -1375,6 +1379,10 @@ int athmhd_newdt(athmhd_t h, const double* cons, const double* bface, int nblock
   int bad;
   std::memcpy(dt_host, hp, 8);
   std::memcpy(&bad, hp + 8, 4);
+  if (std::isnan(*dt_host)) {
+    hipLaunchKernelGGL(k_clear, dim3(1), dim3(64), 0, s, h->d_dtmin, h->d_dtcount, h->d_bad, 4);
+    return fail(h, ATHMHD_EHIP, "the CFL reduction did not end");
+  }
   if (bad != 0)
     return fail(h, ATHMHD_ENONPHYS, "%d non-physical cell evaluations (rho <= 0, P <= 0 or not finite)", bad);
   return ATHMHD_OK;

@@ -262,12 +262,19 @@ constexpr int kDtBlocks = 1024;
 // written as the workgroup's partial result parts[wg] (PARTS = true; a later
 // reduction reads them, so nothing needs clearing before the launch).  The
 // last of total workgroups finishes the reduction (CflEnd).  The atomics are
-// ordered by waiting for their results, which feed the next one, not by
-// fences: a device fence would write back and drop this XCD's L2.  Finishing
+// ordered by waiting for their results (after), not by fences: a device fence
+// would write back and drop this XCD's L2.  Finishing
 // here took two launches out of a chained step and two copies out of newdt
 // (per step: 64^3 97.7 -> 95.9 us, 256^3 3058 -> 2995 us, 1024 batched blocks 3695
 // -> 3648 us).
 constexpr unsigned long long kInfBits = 0x7ff0000000000000ull;
+
+// one, once an atomic's old value has arrived, whatever that value is
+__device__ __forceinline__ unsigned after(unsigned one, unsigned old) {
+  asm volatile("" : "+v"(one) : "v"(old));
+  return one;
+}
+
 template <bool PARTS>
 __device__ __forceinline__ void dt_workgroup_end(double best, int nbad, unsigned long long* dt_bits, int* bad,
                                                  DtPart* parts, int64_t wg, const CflEnd& end, unsigned total) {
@@ -295,10 +302,9 @@ __device__ __forceinline__ void dt_workgroup_end(double best, int nbad, unsigned
       parts[wg].nbad = nb;
       return;
     }
-    unsigned one = 1u;  // plus the sign bits of the atomics' old values, always 0
-    if (m < DBL_MAX)
-      one += (unsigned)(atomicMin(dt_bits, (unsigned long long)__double_as_longlong(m)) >> 63);
-    if (nb) one += (unsigned)atomicAdd(bad, nb) >> 31;
+    unsigned one = 1u;
+    if (m < DBL_MAX) one = after(one, (unsigned)atomicMin(dt_bits, (unsigned long long)__double_as_longlong(m)));
+    if (nb) one = after(one, (unsigned)atomicAdd(bad, nb));
     if (end.count && atomicAdd(end.count, one) == total - 1) {
       atomicExch(end.count, 0u);
       *end.dt = end.cfl * __longlong_as_double((long long)atomicExch(dt_bits, kInfBits));
