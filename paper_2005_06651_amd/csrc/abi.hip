@@ -386,9 +386,14 @@ hipError_t launch_cfl(athmhd_t h, const double* cons, const double* bface, int n
   if (h->levels) {
     hipError_t e =
         launch_newdt(h->g, h->cfg.gamma, cons, bface, 1, h->d_dtmin, h->floors, h->d_bad, CflEnd{}, s);
-    if (e != hipSuccess) return e;
-    return launch_newdt(h->gf, h->cfg.gamma, cons + h->g.cblock, bface + h->g.fblock, 8, h->d_dtmin, h->floors,
-                        h->d_bad, end, s);
+    if (e == hipSuccess)
+      e = launch_newdt(h->gf, h->cfg.gamma, cons + h->g.cblock, bface + h->g.fblock, 8, h->d_dtmin, h->floors,
+                       h->d_bad, end, s);
+    // without the second launch the first one's minimum would stay for the next
+    // reduction (the error may be an older one that this launch only reported)
+    if (e != hipSuccess)
+      hipLaunchKernelGGL(k_clear, dim3(1), dim3(64), 0, s, h->d_dtmin, h->d_dtcount, h->d_bad, 4);
+    return e;
   }
   if (h->batch)
     return launch_newdt_batch(h->d_desc, h->nbatch, h->cfg.gamma, cons, bface, h->d_dtmin, h->floors, h->d_bad, end,
