@@ -591,10 +591,15 @@ __device__ __forceinline__ CharBasis char_basis(const double* w, double bn, doub
   c.ff = c.af * fsqrt(cf2);
   c.ss = c.as * fsqrt(cs2);
   c.iq = frcp(c.ff * c.ff + c.ss * c.ss);
+  // unit vector along the transverse field: split and join are inverse to each
+  // other only for a unit vector, and the square of a field below 1e-154 has
+  // lost bits, so a small one is scaled by a power of two first (exact)
   const bool field = bt2 > 0.0;
-  const double ib = frsq(field ? bt2 : 2.0);
-  c.e1 = (field ? t1 : 1.0) * ib;
-  c.e2 = (field ? t2 : 1.0) * ib;
+  const int up = bt2 < 0x1p-900 ? 600 : 0;
+  const double s1 = field ? ldexp(t1, up) : 1.0, s2 = field ? ldexp(t2, up) : 1.0;
+  const double ib = frsq(s1 * s1 + s2 * s2);
+  c.e1 = s1 * ib;
+  c.e2 = s2 * ib;
   c.sg = bn >= 0.0 ? 1.0 : -1.0;
   const double a = fsqrt(a2);
   c.sra = c.sr * a;
