@@ -478,13 +478,16 @@ __device__ __forceinline__ void ppm_cell(double qa, double qb, double qc, double
     const double d2r = qc - 2.0 * qd + qe;
     // r = limited d2 over d2, in [0, 1].  A tiny d2 (denormal, as in the
     // decaying precursor ahead of a blast wave) has no finite reciprocal:
-    // both are scaled by a power of two first (exact).
+    // both are scaled by a power of two first (exact).  Where the curvatures
+    // disagree the numerator is zero, not r: a stencil that is not a number makes
+    // both edges one, whatever its sign bits.  The offset keeps den = 0 from the
+    // reciprocal and changes no other den (half an ulp of 0x1p-900 is 0x1p-953).
     double num = fmin(fabs(d2), C * fmin(fabs(d2c), fmin(fabs(d2l), fabs(d2r)))), den = fabs(d2);
     const bool same = same_sign(d2, d2c, d2l, d2r);
     const int e = den < 0x1p-900 ? 900 : 0;
     num = ldexp(num, e);
     den = ldexp(den, e);
-    const double r = same && den != 0.0 ? num * frcp(den) : 0.0;
+    const double r = (same ? num : 0.0) * frcp(den + 0x1p-960);
     qm = qc + (qm - qc) * r;
     qp = qc + (qp - qc) * r;
   } else {
@@ -520,7 +523,7 @@ __device__ __forceinline__ void ppm_cell_flat(double qa, double qb, double qc, d
   const int e = den < 0x1p-900 ? 900 : 0;
   num = ldexp(num, e);
   den = ldexp(den, e);
-  const double r = same && den != 0.0 ? num * frcp(den) : 0.0;
+  const double r = (same ? num : 0.0) * frcp(den + 0x1p-960);
   const double dqm = qm - qc, dqp = qp - qc;
   const double mp = fabs(dqp) >= 2.0 * fabs(dqm) ? qc - 2.0 * dqm : qp;
   const double mm = fabs(dqm) >= 2.0 * fabs(mp - qc) ? qc - 2.0 * (mp - qc) : qm;
