@@ -379,8 +379,10 @@ ATHMHD_API int athmhd_batch_tune(athmhd_t h, const double* cons, const double* b
 ATHMHD_API int athmhd_set_floors(athmhd_t h, double dfloor, double pfloor);
 
 /* Number of floor activations (cells and face states) since the previous
- * call, which clears the counter.  A cell or face that several workgroups of
- * the stage kernel evaluate (at tile and segment edges) counts for each.  Synchronises `stream`. */
+ * call, which clears the counter.  The fused kernels count each active cell and
+ * each state of an active cell's lower faces once per stage, however the launch
+ * is planned; the unfused pipeline also counts ghost cells and their faces.
+ * Synchronises `stream`. */
 ATHMHD_API int athmhd_floor_count(athmhd_t h, long long* count, void* stream);
 
 /* enable = 1: athmhd_step records its launches once into a hipGraph (for the

@@ -422,7 +422,11 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
 
   const double i1 = 1.0 / g.dx1, i2 = 1.0 / g.dx2, i3 = 1.0 / g.dx3;
   const double gm1 = sa.gas.gm1;
-  int nbad = 0, nfl = 0;
+  // bit 30: a non-physical cell was met; below it the floor activations: each
+  // active cell (in its own column and segment) and each lower face of one counts
+  // once, whatever the tiles and segments
+  constexpr int kBad = 1 << 30;
+  int seen = 0;
 
   // ---- z window: planes p-LA .. p+LA of the own column
   ZCell win[NW];
@@ -443,8 +447,8 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
       load_raw<MESH>(g, xc, xb, own, ka, raw);
       ka = pos_next<MESH>(g, ka);
       const int f = to_prim<FL>(raw, gm1, sa.fl, w);
-      nbad += f & 1;
-      nfl += f >> 1;
+      if (f & 1) seen |= kBad;
+      if (FL && o > LA) seen += f >> 1;
       to_zcell(w, win[o + 1]);
       if (!RELOAD_BN && o >= LA) {
         bnq[o - LA][0] = raw.b1lo;
@@ -488,8 +492,8 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
     {
       double w[8];
       const int f = to_prim<FL>(pre, gm1, sa.fl, w);
-      nbad += f & 1;
-      nfl += f >> 1;
+      if (f & 1) seen |= kBad;
+      if (FL && p + LA >= k0 && p + LA < kend) seen += f >> 1;
       to_zcell(w, win[NW - 1]);
       if (SAME) {
 #pragma unroll
@@ -567,7 +571,9 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
       if (zface) {
         const double bn3 = bnq[0][2];
         FaceFlux fz;
-        riemann<RS, FL>(zl, zr, bn3, sa.gas, sa.ct_eps, sa.fl, nfl, fz, wz);
+        int hit = 0;
+        riemann<RS, FL>(zl, zr, bn3, sa.gas, sa.ct_eps, sa.fl, hit, fz, wz);
+        if (FL && p < kend) seen += hit;
         // z-frame -> (rho, M1, M2, M3, E); x3-face E2 = -F(B1), E1 = +F(B2)
         fz_cons[0] = fz.rho; fz_cons[1] = fz.mt1; fz_cons[2] = fz.mt2; fz_cons[3] = fz.mn; fz_cons[4] = fz.e;
         e2z = -fz.bt1;
@@ -643,7 +649,9 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
       } else {
         face_states<RECON, CHAR>(sp, PL, row, 1, mapx, 5, sa.gas.gamma, ql, xr);
       }
-      riemann<RS, FL>(ql, xr, bnq[0][0], sa.gas, sa.ct_eps, sa.fl, nfl, fx, wx);
+      int hit = 0;
+      riemann<RS, FL>(ql, xr, bnq[0][0], sa.gas, sa.ct_eps, sa.fl, hit, fx, wx);
+      if (FL && zface && p < kend) seen += hit;
       if (MF && act && p >= k0 && p < kend) put(face_plane<MESH>(g, bp.fm, 0, w0), own.f, fx.rho);
       // x1-face E3 = -F(B2), E2 = +F(B3)
       e3x = -fx.bt1;
@@ -671,7 +679,9 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
     if (ty >= 1) {
       if constexpr (!EDGES) face_states<RECON, CHAR>(sp, PL, row, PW, mapy, 6, sa.gas.gamma, yl, yr);
       FaceFlux fy;
-      riemann<RS, FL>(yl, yr, bnq[0][1], sa.gas, sa.ct_eps, sa.fl, nfl, fy, wy);
+      int hit = 0;
+      riemann<RS, FL>(yl, yr, bnq[0][1], sa.gas, sa.ct_eps, sa.fl, hit, fy, wy);
+      if (FL && zface && p < kend) seen += hit;
       if (MF && act && p >= k0 && p < kend) put(face_plane<MESH>(g, bp.fm, 1, w0), own.f, fy.rho);
       sx[(X_FY + 0) * NT + tid] = fy.rho;
       sx[(X_FY + 1) * NT + tid] = fy.mt2;  // M1
@@ -797,8 +807,8 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
   if (act && kend >= k0)
     face_update<MESH>(g, sc, tid, BX, NT, own.f, kend, MESH ? kr1 : Pos{kend, 0},
                       MESH ? kr2 : Pos{kend - 1, 0}, k0, kend, i1, i2, i3, bdt, pwb, acc_prev, ob);
-  if (nbad && act) atomicAdd(sa.bad, 1);
-  if (nfl && act) add_floor_count(sa.bad, (unsigned long long)nfl);
+  if ((seen & kBad) && act) atomicAdd(sa.bad, 1);
+  if (FL && (seen & ~kBad) && act) add_floor_count(sa.bad, (unsigned long long)(seen & ~kBad));
 }
 
 // Uniform blocks: one workgroup per (tile, x3 segment, block), XCD-aware:
