@@ -377,12 +377,14 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
   constexpr int BX = T::BX, BY = T::BY, NT = T::NT, TX = T::TX, TY = T::TY;
   using S = Smem<LA, T>;
   constexpr int PW = S::PW, PL = S::PL;
-  const double* __restrict__ xc = bp.xc;
-  const double* __restrict__ xb = bp.xb;
-  const double* __restrict__ unc = bp.unc;
-  const double* __restrict__ unb = bp.unb;
-  double* __restrict__ oc = bp.oc;
-  double* __restrict__ ob = bp.ob;
+  // the last stage's output is U^n's own array, and the first stage's input is
+  // U^n: nothing here may be called unaliased
+  const double* const xc = bp.xc;
+  const double* const xb = bp.xb;
+  const double* const unc = bp.unc;
+  const double* const unb = bp.unb;
+  double* const oc = bp.oc;
+  double* const ob = bp.ob;
   const double bdt = sa.dt_dev ? sa.beta * *sa.dt_dev : sa.cf.bdt;
 
   const int tid = threadIdx.x;
