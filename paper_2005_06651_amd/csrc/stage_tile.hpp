@@ -276,7 +276,7 @@ constexpr int exchange_slots() { return RECON >= 2 ? X_N - 1 : X_N; }
 // leaves the partial B1, B2 of plane q in bacc[5], bacc[6].  pwb holds the
 // pointwise terms (g1 U^n + g0 X) of B1, B2 at q-1 and B3 at q.
 template <int MESH>
-__device__ __forceinline__ void face_update(const Geo& g, const double* __restrict__ sc, int tid, int BX, int NT,
+__device__ __forceinline__ void face_update(const Geo& g, const double* sc, int tid, int BX, int NT,
                                             unsigned f, int q, Pos at_q, Pos below, int k0, int kend, double i1,
                                             double i2, double i3,
                                             double bdt, const double* pwb, double* bacc, double* ob) {
@@ -304,7 +304,7 @@ __device__ __forceinline__ void face_update(const Geo& g, const double* __restri
 // nrm: slot of the cell-centred normal field).
 // own_edges: left and right edge of the own cell.
 template <int RECON, bool FLAT>
-__device__ __forceinline__ void own_edges(const double* __restrict__ sp, int PL, int row, int st, const int (&map)[7],
+__device__ __forceinline__ void own_edges(const double* sp, int PL, int row, int st, const int (&map)[7],
                                           double* lo, double* hi) {
   constexpr int NW = 2 * RECON + 1;
 #pragma unroll
@@ -323,7 +323,7 @@ __device__ __forceinline__ void own_edges(const double* __restrict__ sp, int PL,
 
 // face_states: right edge of the cell below and left edge of the own cell.
 template <int RECON, bool CHAR>
-__device__ __forceinline__ void face_states(const double* __restrict__ sp, int PL, int row, int st,
+__device__ __forceinline__ void face_states(const double* sp, int PL, int row, int st,
                                             const int (&map)[7], int nrm, double gamma, double* ql, double* qr) {
   constexpr int NW = 2 * RECON + 1;
   if constexpr (CHAR) {
@@ -370,8 +370,8 @@ __device__ __forceinline__ void face_states(const double* __restrict__ sp, int P
 template <int RECON, int RS, class T, bool FL, int MESH = 0, bool MF = false, bool SAME = false, bool CHAR = false,
           bool LONE = false>
 __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, const StageArgs& sa, int tile_x,
-                                           int tile_y, int k0, int kend, double* __restrict__ sp,
-                                           double* __restrict__ sx, double* __restrict__ sc) {
+                                           int tile_y, int k0, int kend, double* sp,
+                                           double* sx, double* sc) {
   constexpr int LA = RECON;  // cells of look-ahead / extra LDS rings: DC 0, PLM 1, PPM 2
   constexpr int NW = 2 * LA + 1;
   constexpr int BX = T::BX, BY = T::BY, NT = T::NT, TX = T::TX, TY = T::TY;
