@@ -121,7 +121,8 @@ typedef struct {
  * Roe & Balsara 1996).  DC (the VL2 predictor) is unchanged.  With PPM,
  * or DC configured, such a handle runs its stages (but for the DC predictor)
  * on the unfused kernel pipeline whatever kernel_path says.  A step leaves the
- * ghost entries of its input filled.
+ * ghost entries of its input filled (RK1, which steps in a register and copies
+ * it back, leaves them as they were).
  * ATHMHD_EUNSUP with passive scalars, on athmhd_create_mesh and
  * athmhd_create_batch, and from athmhd_step_vjp. */
 
@@ -154,8 +155,10 @@ ATHMHD_API int athmhd_step(athmhd_t h, double* cons, double* bface, double dt, i
  * dx_d / (|v_d| + c_f,d), the value athmhd_newdt would return for it (+inf
  * when no cell gives a finite limit), computed by the CFL reduction of
  * athmhd_newdt queued after the step.  nbad_dev (device int, or NULL): the
- * number of non-physical cells met by the step and the reduction, after which
- * the handle's counter is cleared; with NULL the count stays in the handle
+ * number of non-physical cells met by the step and the reduction (a stage
+ * counts the cells that one thread meets as one, so that only zero or not is a
+ * property of the state), after which the handle's counter is cleared; with
+ * NULL the count stays in the handle
  * and the next athmhd_newdt reports it.  No host synchronisation: a run of
  * steps is queued without waiting.  Graph mode (athmhd_set_graph) does not
  * apply.  Asynchronous on `stream`. */
@@ -290,8 +293,9 @@ ATHMHD_API int athmhd_prim2cons_vjp(athmhd_t h, const double* prim, const double
  *     in place; with passive scalars, or where a layer of blocks along x3 holds
  *     4 GiB or more per array, the library exchanges the ghost entries before
  *     every stage instead (device kernel).  Either way athmhd_step leaves the
- *     ghost entries of its input that its first stage reaches filled
- *     (athmhd_fill_ghosts refreshes them after it).
+ *     ghost entries of its input that its first stage reaches filled (RK1,
+ *     which steps in a register and copies it back, leaves them as they were;
+ *     athmhd_fill_ghosts refreshes them after a step).
  *   - athmhd_newdt, athmhd_prim2cons and the floors read the upper faces of a
  *     block's boundary cells from the neighbouring block, so they do not
  *     depend on ghost entries.
