@@ -236,7 +236,7 @@ __global__ void __launch_bounds__(kT) k_adj_face_fwd(Adj a, const double* __rest
 // cotangents of each face and gathering them in k_adj_cell moved 56 more slots
 // per stage.
 //
-// The lines along D (kSpan cells of x1 side by side) are laid end to end, each
+// The lines along D (kSpan of them side by side, x1 fastest) are laid end to end, each
 // with the faces that its ends take from the periodic images (kLow before and
 // kHigh after); a workgroup takes kRows consecutive faces and completes the
 // cells with kLow of them before and kHigh after: whatever a line's length, no
@@ -263,8 +263,7 @@ struct Line {
 template <int D, int RECON>
 int64_t line_groups(const Adj& a) {
   typedef Line<D, RECON> L;
-  const int64_t lines =
-      D == 0 ? (int64_t)a.n[1] * a.n[2] : (int64_t)((a.n[0] + L::kSpan - 1) / L::kSpan) * a.n[3 - D];
+  const int64_t lines = (a.nc / a.n[D] + L::kSpan - 1) / L::kSpan;
   return (lines * (a.n[D] + L::kLow + L::kHigh) + L::kDone - 1) / L::kDone;
 }
 
@@ -283,17 +282,16 @@ __global__ void __launch_bounds__((Line<D, RECON>::kB)) __attribute__((amdgpu_wa
   const int row = (int)threadIdx.x / S, span = a.n[D] + L_::kLow + L_::kHigh;
   const int64_t seq = (int64_t)wg * L_::kDone + row;
   const int line = (int)(seq / span), pos = (int)(seq % span) - L_::kLow;
-  const int groups = D == 0 ? 1 : (a.n[0] + S - 1) / S;  // of x1, per line of the two other directions
-  const int other = line / groups;
+  // the line among those of the two other directions, the lower one fastest
+  constexpr int A = D == 0 ? 1 : 0, B = 3 - D - A;
+  const int column = line * S + (int)threadIdx.x % S;
   Cell c;
-  c.x[0] = D == 0 ? wrapn(pos, a.n[0]) : (line % groups) * S + (int)threadIdx.x % S;
-  c.x[1] = D == 1 ? wrapn(pos, a.n[1]) : (D == 0 ? other % a.n[1] : other);
-  c.x[2] = D == 2 ? wrapn(pos, a.n[2]) : (D == 0 ? other / a.n[1] : other);
-  const bool stored = c.x[0] < a.n[0] && c.x[1] < a.n[1] && c.x[2] < a.n[2];
+  c.x[D] = wrapn(pos, a.n[D]);
+  c.x[A] = column % a.n[A];
+  c.x[B] = column / a.n[A];
+  const bool stored = c.x[B] < a.n[B];
   // threads beyond the block repeat a cell of it
-  c.x[0] = min(c.x[0], a.n[0] - 1);
-  c.x[1] = min(c.x[1], a.n[1] - 1);
-  c.x[2] = min(c.x[2], a.n[2] - 1);
+  c.x[B] = min(c.x[B], a.n[B] - 1);
   const bool mine = stored && pos >= 0 && pos < a.n[D] && row >= L_::kLow && row < L_::kLow + L_::kDone;
   const int t = c.t = c.x[0] + c.x[1] * a.st[1] + c.x[2] * a.st[2];
   const double* fb = xb + blockIdx.y * a.g.fblock;
