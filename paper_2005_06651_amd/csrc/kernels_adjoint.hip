@@ -240,7 +240,10 @@ __global__ void __launch_bounds__(kT) k_adj_face_fwd(Adj a, const double* __rest
 // with the faces that its ends take from the periodic images (kLow before and
 // kHigh after); a workgroup takes kRows consecutive faces and completes the
 // cells with kLow of them before and kHigh after: whatever a line's length, no
-// face is idle but those.  Along x1 a wave is a workgroup, which waits for
+// face is idle but those.  Where it takes fewer workgroups, a workgroup holds
+// whole lines instead, whose ends meet in LDS: on lines of one cell the images
+// are three of four faces (256 x 256 x 1 PLM 185 -> 162 us a step, donor cell
+// 151 -> 140).  Along x1 a wave is a workgroup, which waits for
 // nothing but itself; across x1 256 threads of 8 cells (PLM: 29 of 32 rows
 // complete a cell) or 16 (donor cell: 15 of 16) measured best of 8 and 16
 // cells on 128, 256 and 512 threads.
@@ -259,17 +262,21 @@ struct Line {
   static constexpr int kDone = kRows - kLow - kHigh;  // cells a workgroup completes
 };
 
-// number of workgroups
+// number of workgroups, and in whole the lines each holds (0: laid end to end)
 template <int D, int RECON>
-int64_t line_groups(const Adj& a) {
+int64_t line_groups(const Adj& a, int* whole) {
   typedef Line<D, RECON> L;
   const int64_t lines = (a.nc / a.n[D] + L::kSpan - 1) / L::kSpan;
-  return (lines * (a.n[D] + L::kLow + L::kHigh) + L::kDone - 1) / L::kDone;
+  const int64_t chained = (lines * (a.n[D] + L::kLow + L::kHigh) + L::kDone - 1) / L::kDone;
+  const int fit = L::kRows / a.n[D];
+  const int64_t held = fit > 0 ? (lines + fit - 1) / fit : chained;
+  *whole = held < chained ? fit : 0;
+  return std::min(held, chained);
 }
 
 template <int D, int RECON, int RS>
 __global__ void __launch_bounds__((Line<D, RECON>::kB)) __attribute__((amdgpu_waves_per_eu(2)))
-    k_adj_face_bwd(Adj a, int per_xcd, const double* __restrict__ xb, const double* __restrict__ V,
+    k_adj_face_bwd(Adj a, int per_xcd, int whole, const double* __restrict__ xb, const double* __restrict__ V,
                    double* __restrict__ scr) {
   constexpr int T1 = (D + 1) % 3, T2 = (D + 2) % 3;
   typedef Line<D, RECON> L_;
@@ -279,20 +286,24 @@ __global__ void __launch_bounds__((Line<D, RECON>::kB)) __attribute__((amdgpu_wa
   // (line, position) of this thread's face; consecutive workgroups, which share
   // lines and planes, run on one XCD
   const int wg = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
-  const int row = (int)threadIdx.x / S, span = a.n[D] + L_::kLow + L_::kHigh;
-  const int64_t seq = (int64_t)wg * L_::kDone + row;
-  const int line = (int)(seq / span), pos = (int)(seq % span) - L_::kLow;
+  const int row = (int)threadIdx.x / S, n = a.n[D];
+  const int low = whole ? 0 : L_::kLow, span = whole ? n : n + L_::kLow + L_::kHigh;
+  const int done = whole ? whole * n : L_::kDone;
+  const int64_t seq = (int64_t)wg * done + row;
+  const int line = (int)(seq / span), pos = (int)(seq % span) - low;
   // the line among those of the two other directions, the lower one fastest
   constexpr int A = D == 0 ? 1 : 0, B = 3 - D - A;
   const int column = line * S + (int)threadIdx.x % S;
   Cell c;
-  c.x[D] = wrapn(pos, a.n[D]);
+  c.x[D] = wrapn(pos, n);
   c.x[A] = column % a.n[A];
   c.x[B] = column / a.n[A];
   const bool stored = c.x[B] < a.n[B];
   // threads beyond the block repeat a cell of it
   c.x[B] = min(c.x[B], a.n[B] - 1);
-  const bool mine = stored && pos >= 0 && pos < a.n[D] && row >= L_::kLow && row < L_::kLow + L_::kDone;
+  const bool mine = stored && pos >= 0 && pos < n && row >= low && row < low + done;
+  // the ends of whole lines, a bit per lane: no vector register through the solver
+  const unsigned long long firsts = __ballot(whole && pos == 0), lasts = __ballot(whole && pos == n - 1);
   const int t = c.t = c.x[0] + c.x[1] * a.st[1] + c.x[2] * a.st[2];
   const double* fb = xb + blockIdx.y * a.g.fblock;
   const double* v = V + blockIdx.y * (8 * a.ss);
@@ -390,7 +401,10 @@ __global__ void __launch_bounds__((Line<D, RECON>::kB)) __attribute__((amdgpu_wa
   else hlle_vjp(L, R, bn, a.gas, a.ct_eps, Fb, w_b, Lb, Rb, bn_b);
   const double lb[7] = {Lb.rho, Lb.vn, Lb.vt1, Lb.vt2, Lb.p, Lb.bt1, Lb.bt2};
   const double rb[7] = {Rb.rho, Rb.vn, Rb.vt1, Rb.vt2, Rb.p, Rb.bt1, Rb.bt2};
-  const int lo = max(tid - S, 0), hi = min(tid + S, kB - 1);
+  // the threads of the cells before and after (a whole line's ends: each other)
+  const bool first = (firsts >> (tid & 63)) & 1, last = (lasts >> (tid & 63)) & 1;
+  const int lo = min(max(first ? tid + (n - 1) * S : tid - S, 0), kB - 1);
+  const int hi = min(max(last ? tid - (n - 1) * S : tid + S, 0), kB - 1);
 #pragma unroll
   for (int m = 0; m < 7; ++m) xl[m * kB + tid] = lb[m];
   if (mine) s[(S_BN + D) * a.ss + t] = bn_b;
@@ -697,10 +711,11 @@ void face_pair(const Adj& a, int rs, dim3 grid, const double* xb, const double* 
     if (rs == 1) hipLaunchKernelGGL((k_adj_face_fwd<D, RECON, 1>), grid, dim3(kT), 0, s, a, xb, scr);
     else hipLaunchKernelGGL((k_adj_face_fwd<D, RECON, 0>), grid, dim3(kT), 0, s, a, xb, scr);
   } else {
-    const int per_xcd = (int)((line_groups<D, RECON>(a) + 7) / 8);
+    int whole;
+    const int per_xcd = (int)((line_groups<D, RECON>(a, &whole) + 7) / 8);
     const dim3 lines(8u * (unsigned)per_xcd, grid.y);
-    if (rs == 1) hipLaunchKernelGGL((k_adj_face_bwd<D, RECON, 1>), lines, dim3(Line<D, RECON>::kB), 0, s, a, per_xcd, xb, V, scr);
-    else hipLaunchKernelGGL((k_adj_face_bwd<D, RECON, 0>), lines, dim3(Line<D, RECON>::kB), 0, s, a, per_xcd, xb, V, scr);
+    if (rs == 1) hipLaunchKernelGGL((k_adj_face_bwd<D, RECON, 1>), lines, dim3(Line<D, RECON>::kB), 0, s, a, per_xcd, whole, xb, V, scr);
+    else hipLaunchKernelGGL((k_adj_face_bwd<D, RECON, 0>), lines, dim3(Line<D, RECON>::kB), 0, s, a, per_xcd, whole, xb, V, scr);
   }
 }
 
