@@ -404,9 +404,9 @@ class Solver:
 class MeshSolver(Solver):
     """A coupled mesh: mesh = (nbx, nby, nbz) equal blocks of n cells tiling one
     periodic domain; block b = bx + nbx (by + nby bz).  Tensors hold all
-    blocks: cons (nb, 5 + nscalars, N3, N2, N1), bface (nb, 3, N3+1, N2+1, N1+1).  Before
-    every stage the library exchanges ghost cells and faces between the
-    blocks (see athmhd_create_mesh)."""
+    blocks: cons (nb, 5 + nscalars, N3, N2, N1), bface (nb, 3, N3+1, N2+1, N1+1).  The
+    stages read neighbouring blocks in place, or with passive scalars after an
+    exchange of ghost cells and faces (see athmhd_create_mesh)."""
 
     def __init__(self, n, mesh, nghost, dx, gamma, recon="plm", riemann="hlld", integrator="vl2", cfl=0.3,
                  ct_eps=0.0, nscalars=0):

@@ -415,8 +415,9 @@ FusedPlan stage_plan(athmhd_t h, int recon, int nblocks) {
 // Characteristic PLM and the donor-cell predictor beside characteristic PLM or
 // PPM run fused; characteristic PPM does not (its eigenvector split beside the
 // five-plane window spills 157 registers of the fused kernel, and one variant
-// of it, HLLE without floors, came out of the compiler wrong), nor does a
-// handle configured with donor cell, which keeps the pipeline's results.
+// of it, HLLE without floors, gave wrong results from a cause that was not
+// found), nor does a handle configured with donor cell, which keeps the
+// pipeline's results.
 bool stage_unfused(athmhd_t h, int recon) {
   if (h->cfg.kernel_path == 1 || h->levels) return true;
   return h->unfused && !(h->cfg.recon == ATHMHD_RECON_PPM && recon == ATHMHD_RECON_DC);

@@ -30,13 +30,14 @@ static double rounds_small(int64_t wgs, int cus, int recon, bool lone) {
 // Thread tile and x3 segment length of a launch: the pair with the least
 // planes x rounds.  A segment of kz planes costs kz + 2 plane iterations and a
 // window start-up; short segments repeat more of them, long ones leave the
-// last round of workgroups nearly empty or the chip unfilled.  Measured with
-// the rule before (34 x 15 only, kz in 4, 8, .. 32 or 64) and now, per step:
-// 64^3 VL2+PLM 98 -> 83 us, 96^3 252 -> 193 us, 192^3 1415 -> 1242 us, 32^3 RK3+PPM
-// 363 -> 150 us (124 -> 104 sustained with the lone variant, 48^3 201 -> 165, 56^3
-// 280 -> 227, 64^3 298 -> 290), 200x150x131 RK3+PPM+HLLE 3.4 -> 2.6 ms; 256^3 VL2+PLM stays on
-// 34 x 15 and 32 planes (2.75 ms; 18 x 14: 2.94); RK3+PPM runs on 18 x 14 (9.1
-// and 8.9 ms).
+// last round of workgroups nearly empty or the chip unfilled.  The same kernels
+// with the rule before (34 x 15 only, kz in 4, 8, .. 32 or 64) and now, sustained
+// steps of a smooth state without the CFL pass: VL2+PLM at 64^3 91 -> 78 us, 96^3
+// 263 -> 178, 192^3 1350 -> 1207; RK3+PPM at 32^3 325 -> 102, 48^3 328 -> 162, 64^3
+// 337 -> 283, 200x150x131 with HLLE 2873 -> 2255.  256^3 VL2+PLM stays on 34 x 15
+// and 32 planes (2.66 ms; 18 x 14: 2.98); RK3+PPM runs on 18 x 14 (9.9 ms; 34 x 15:
+// 10.1).  The lone variant, without and with: 32^3 122 -> 102 us, 48^3 196 -> 162,
+// 56^3 268 -> 222.
 FusedPlan fused_plan(const Geo& geo, int recon, int nb, int cus, int kz_fixed) {
   FusedPlan best{false, 1, false};
   Geo g = geo;

@@ -429,7 +429,6 @@ __device__ __forceinline__ double vl_slope(double qm, double q0, double qp) {
   return pr > 0.0 ? 2.0 * pr * frcp(dm + dp) : 0.0;
 }
 
-// Colella & Sekora (2008) extremum-preserving PPM on a uniform grid.
 // Whether all of a, b, c (, d) share the sign bit of a: integer operations on
 // their high words instead of eight compares and the mask logic that joins
 // them.  A zero among them needs no test of its own: the limited value is the
@@ -447,6 +446,8 @@ __device__ __forceinline__ bool same_sign(double a, double b, double c, double d
   return ((high_word(a) ^ high_word(b)) | (high_word(a) ^ high_word(c)) | (high_word(a) ^ high_word(d))) >= 0;
 }
 
+// Colella & Sekora (2008) extremum-preserving PPM on a uniform grid: the value
+// of smallest magnitude among a, 1.25 b and 1.25 c where their signs agree, else 0.
 __device__ __forceinline__ double cs_lim3(double a, double b, double c) {
   constexpr double C = 1.25;
   const double m = fmin(fabs(a), C * fmin(fabs(b), fabs(c)));

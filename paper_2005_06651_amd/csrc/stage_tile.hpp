@@ -34,9 +34,10 @@
 //     barrier and used after the corner EMFs;
 //   * planes are addressed by a scalar base and a 32-bit vector offset.
 // Before, a plane exposed three to five memory latencies one after the other
-// (loads waited for inside the branch that issued them).  256^3, per
-// step: VL2+PLM+HLLD 3.06 -> 2.74 ms, RK2+DC 2.84 -> 2.45 ms,
-// RK3+PPM 13.5 -> 12.1 ms.
+// (loads waited for inside the branch that issued them).  That and the later
+// changes to this kernel together, sustained steps of a smooth 256^3 state without
+// the CFL pass: VL2+PLM+HLLD 3.00 -> 2.66 ms, RK2+DC 2.72 -> 2.32 ms, RK3+PPM
+// 16.0 -> 9.9 ms.
 #pragma once
 
 #include "stage_args.hpp"
@@ -474,9 +475,9 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
   // where the look-ahead plane's loads are issued: before the x1-face (DC),
   // between the x1- and the x2-face (PLM), after the x2-face (PPM).  Earlier
   // hides more of their latency, later keeps 22 registers free through a
-  // Riemann problem.  256^3 step with each of the three places: RK2+DC 2.42 /
-  // 2.45 / 2.48 ms, VL2+PLM 2.76 / 2.74 / 2.77 ms, RK3+PPM 12.36 / 12.14 / 12.23
-  // ms (and 11.38 / 11.37 / 11.17 ms on 18 x 14 threads).
+  // Riemann problem.  Sustained steps of a smooth 256^3 state without the CFL
+  // pass, with each of the three places: RK2+DC 2.33 / 2.33 / 2.39 ms, VL2+PLM 2.68 /
+  // 2.65 / 2.67 ms, RK3+PPM (18 x 14 threads) 11.10 / 10.14 / 9.92 ms.
   constexpr int PF = RECON;
   double pwb[3] = {0.0, 0.0, 0.0};
 #pragma unroll
@@ -619,11 +620,11 @@ __device__ __forceinline__ void stage_tile(const Geo& g, const BlockPtrs& bp, co
     // the left edge is its own face's right state, the right edge goes to the
     // next thread through the slots that the face's results take afterwards.
     // Two more barriers a plane, for a quarter of the loop's instructions
-    // (6171 -> 4682): 200x150x131 RK3+PPM+HLLE 2.81 -> 2.37 ms per step, 512^3 blast
-    // 82.0 -> 77.5 ms.  With PLM a slope is cheap, and it pays only where the
-    // other workgroup of the CU fills the barriers: 1024 batched blocks 3.60 ->
-    // 3.49 ms, but 256^3 on the 8-wave tile 2.93 -> 2.96 ms, characteristic PLM at
-    // 192^3 (spills) 1.93 -> 1.98 ms.
+    // (6171 -> 4682): 200x150x131 RK3+PPM+HLLE 2.81 -> 2.36 ms per chained step,
+    // 512^3 blast 81.5 -> 76.8 ms.  With PLM a slope is cheap, and it pays less:
+    // 1024 batched blocks, where the other workgroup of the CU fills the barriers,
+    // 3.70 -> 3.61 ms; on the 8-wave tile 256^3 takes 3.03 ms either way and 512
+    // blocks of 32^3 as one mesh 3.59 ms, or 3.51 with edges through LDS.
     constexpr bool EDGES = RECON >= 2 || (RECON == 1 && !CHAR && NT != TileU::NT);
     const int row = (ty + LA) * PW + tx + LA;  // own cell in the primitive plane
     // x-frame order: rho, v1, v2, v3, P, B2, B3; y-frame order: rho, v2, v3, v1, P, B3, B1

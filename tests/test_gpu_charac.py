@@ -1,6 +1,7 @@
 """Characteristic reconstruction on the GPU (Sec. 3.2.1, C = L W; PLM, PPM):
-the unfused pipeline's flux kernels project onto the characteristic
-variables of each cell, limit per wave family and project back.  Checked
+the fused stage kernel (PLM) and the unfused pipeline's flux kernels (PPM) project
+onto the characteristic variables of each cell, limit per wave family and project
+back.  Checked
 against the oracle at the 1e-12 bar on ragged blocks and on Brio & Wu's
 shock tube, with donor cell unchanged and reverse mode refused.
 """

@@ -1,6 +1,6 @@
-"""Coupled mesh: equal blocks tiling one periodic domain, with the ghost
-cells and faces exchanged between blocks on the device before every stage
-(Sec. 2.1.1).  Split into blocks, the domain must step as the single block
+"""Coupled mesh: equal blocks tiling one periodic domain, whose stages read
+neighbouring blocks in place (with passive scalars, ghost cells and faces
+exchanged on the device before every stage; Sec. 2.1.1).  Split into blocks, the domain must step as the single block
 that covers it: the same kernels on the same values, so the dt agrees
 exactly and the state to 1e-14 (the x3 segments of the fused kernel fall on
 other planes, and the compiler's copies of the first and last plane of a
