@@ -592,7 +592,9 @@ __device__ __forceinline__ CharBasis char_basis(const double* w, double bn, doub
   const double id = frcp(split ? d : 1.0);
   c.af = split ? fsqrt(fmin(1.0, fmax(0.0, (a2 - cs2) * id))) : 1.0;
   c.as = split ? fsqrt(fmin(1.0, fmax(0.0, (cf2 - a2) * id))) : 0.0;
-  c.ff = c.af * fsqrt(cf2);
+  // a cell without a sound speed (P < 0, or not a number) has no waves: its edges
+  // are not numbers either (fsqrt alone would give 0)
+  c.ff = a2 >= 0.0 ? c.af * fsqrt(cf2) : __builtin_nan("");
   c.ss = c.as * fsqrt(cs2);
   c.iq = frcp(c.ff * c.ff + c.ss * c.ss);
   // unit vector along the transverse field: split and join are inverse to each
@@ -614,8 +616,11 @@ __device__ __forceinline__ CharBasis char_basis(const double* w, double bn, doub
 // wave amplitudes of dw: fast -+, slow -+, Alfven -+, entropy
 __device__ __forceinline__ void char_split(const CharBasis& c, const double* dw, double* x) {
   const double par = c.sg * (c.e1 * dw[2] + c.e2 * dw[3]), per = c.e2 * dw[2] - c.e1 * dw[3];
-  const double p = dw[4] * c.igp, b = (c.e1 * dw[5] + c.e2 * dw[6]) * c.isra;
-  const double al = (c.e1 * dw[6] - c.e2 * dw[5]) * (c.sg * c.isr);
+  // a neighbour that is not finite, which shows in its pressure, makes every
+  // amplitude a NaN, and so every slope 0
+  const double q = dw[4] * c.igp, nan = 0.0 * q;
+  const double p = q + nan, b = (c.e1 * dw[5] + c.e2 * dw[6]) * c.isra;
+  const double al = (c.e1 * dw[6] - c.e2 * dw[5]) * (c.sg * c.isr) + nan;
   const double fs = c.af * p + c.as * b, ss = c.as * p - c.af * b;
   const double fd = (c.ff * dw[1] - c.ss * par) * c.iq, sd = (c.ss * dw[1] + c.ff * par) * c.iq;
   x[0] = 0.5 * (fs - fd);
