@@ -242,17 +242,17 @@ __global__ void __launch_bounds__(kT) k_adj_face_fwd(Adj a, const double* __rest
 // cells with kLow of them before and kHigh after: whatever a line's length, no
 // face is idle but those.  Where it takes fewer workgroups, a workgroup holds
 // whole lines instead, whose ends meet in LDS: on lines of one cell the images
-// are three of four faces (256 x 256 x 1 PLM 185 -> 162 us a step, donor cell
-// 151 -> 140).  Along x1 a wave is a workgroup, which waits for
+// are three of four faces (256 x 256 x 1 PLM 185 -> 164 us a step, donor cell
+// 151 -> 138).  Along x1 a wave is a workgroup, which waits for
 // nothing but itself; across x1 256 threads of 8 cells (PLM: 29 of 32 rows
 // complete a cell) or 16 (donor cell: 15 of 16) measured best of 8 and 16
 // cells on 128, 256 and 512 threads.
 //
 // Two waves per SIMD (256 registers): the sweep through the solver needs them,
 // so the slopes' differences wait for it in LDS (read again from memory they
-// cost 35 us of 280).  PLM on a 128^3 block: 189 us along x1, 243 along x2 and
-// x3, and 178 in k_adj_cell; the two-pass form took 206, 202, 192 and 400.
-// Donor cell 149, 173, 178 and 178; before 185, 187, 187 and 277.
+// cost 35 us of 280).  PLM on a 128^3 block: 190 us along x1, 240 along x2, 233
+// along x3, and 175 in k_adj_cell; the two-pass form took 206, 202, 192 and 400.
+// Donor cell 152, 180, 178 and 175; before 185, 187, 187 and 277.
 template <int D, int RECON>
 struct Line {
   static constexpr int kSpan = D == 0 ? 1 : (RECON == 1 ? 8 : 16);
@@ -274,7 +274,9 @@ int64_t line_groups(const Adj& a, int* whole) {
   return std::min(held, chained);
 }
 
-template <int D, int RECON, int RS>
+// WHOLE: a workgroup holds `whole` lines (a kernel of its own: as a run-time
+// choice it cost the donor-cell HLLD form 1.4 % on a 128^3 block)
+template <int D, int RECON, int RS, bool WHOLE>
 __global__ void __launch_bounds__((Line<D, RECON>::kB)) __attribute__((amdgpu_waves_per_eu(2)))
     k_adj_face_bwd(Adj a, int per_xcd, int whole, const double* __restrict__ xb, const double* __restrict__ V,
                    double* __restrict__ scr) {
@@ -287,8 +289,8 @@ __global__ void __launch_bounds__((Line<D, RECON>::kB)) __attribute__((amdgpu_wa
   // lines and planes, run on one XCD
   const int wg = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
   const int row = (int)threadIdx.x / S, n = a.n[D];
-  const int low = whole ? 0 : L_::kLow, span = whole ? n : n + L_::kLow + L_::kHigh;
-  const int done = whole ? whole * n : L_::kDone;
+  const int low = WHOLE ? 0 : L_::kLow, span = WHOLE ? n : n + L_::kLow + L_::kHigh;
+  const int done = WHOLE ? whole * n : L_::kDone;
   const int64_t seq = (int64_t)wg * done + row;
   const int line = (int)(seq / span), pos = (int)(seq % span) - low;
   // the line among those of the two other directions, the lower one fastest
@@ -303,7 +305,7 @@ __global__ void __launch_bounds__((Line<D, RECON>::kB)) __attribute__((amdgpu_wa
   c.x[B] = min(c.x[B], a.n[B] - 1);
   const bool mine = stored && pos >= 0 && pos < n && row >= low && row < low + done;
   // the ends of whole lines, a bit per lane: no vector register through the solver
-  const unsigned long long firsts = __ballot(whole && pos == 0), lasts = __ballot(whole && pos == n - 1);
+  const unsigned long long firsts = WHOLE ? __ballot(pos == 0) : 0ull, lasts = WHOLE ? __ballot(pos == n - 1) : 0ull;
   const int t = c.t = c.x[0] + c.x[1] * a.st[1] + c.x[2] * a.st[2];
   const double* fb = xb + blockIdx.y * a.g.fblock;
   const double* v = V + blockIdx.y * (8 * a.ss);
@@ -402,7 +404,7 @@ __global__ void __launch_bounds__((Line<D, RECON>::kB)) __attribute__((amdgpu_wa
   const double lb[7] = {Lb.rho, Lb.vn, Lb.vt1, Lb.vt2, Lb.p, Lb.bt1, Lb.bt2};
   const double rb[7] = {Rb.rho, Rb.vn, Rb.vt1, Rb.vt2, Rb.p, Rb.bt1, Rb.bt2};
   // the threads of the cells before and after (a whole line's ends: each other)
-  const bool first = (firsts >> (tid & 63)) & 1, last = (lasts >> (tid & 63)) & 1;
+  const bool first = WHOLE && ((firsts >> (tid & 63)) & 1), last = WHOLE && ((lasts >> (tid & 63)) & 1);
   const int lo = min(max(first ? tid + (n - 1) * S : tid - S, 0), kB - 1);
   const int hi = min(max(last ? tid - (n - 1) * S : tid + S, 0), kB - 1);
 #pragma unroll
@@ -713,9 +715,14 @@ void face_pair(const Adj& a, int rs, dim3 grid, const double* xb, const double* 
   } else {
     int whole;
     const int per_xcd = (int)((line_groups<D, RECON>(a, &whole) + 7) / 8);
-    const dim3 lines(8u * (unsigned)per_xcd, grid.y);
-    if (rs == 1) hipLaunchKernelGGL((k_adj_face_bwd<D, RECON, 1>), lines, dim3(Line<D, RECON>::kB), 0, s, a, per_xcd, whole, xb, V, scr);
-    else hipLaunchKernelGGL((k_adj_face_bwd<D, RECON, 0>), lines, dim3(Line<D, RECON>::kB), 0, s, a, per_xcd, whole, xb, V, scr);
+    const dim3 lines(8u * (unsigned)per_xcd, grid.y), wg(Line<D, RECON>::kB);
+    if (whole) {
+      if (rs == 1) hipLaunchKernelGGL((k_adj_face_bwd<D, RECON, 1, true>), lines, wg, 0, s, a, per_xcd, whole, xb, V, scr);
+      else hipLaunchKernelGGL((k_adj_face_bwd<D, RECON, 0, true>), lines, wg, 0, s, a, per_xcd, whole, xb, V, scr);
+    } else {
+      if (rs == 1) hipLaunchKernelGGL((k_adj_face_bwd<D, RECON, 1, false>), lines, wg, 0, s, a, per_xcd, 0, xb, V, scr);
+      else hipLaunchKernelGGL((k_adj_face_bwd<D, RECON, 0, false>), lines, wg, 0, s, a, per_xcd, 0, xb, V, scr);
+    }
   }
 }
 
